@@ -217,8 +217,8 @@ qs_status qs_expect_pauli_sum_noalloc(qs_state s, const uint64_t *x, const uint6
 
 /* ------------------------------------------------------------ batches */
 /* A batch of independent states (uneven qubit counts, 1 <= n_i <= 26),
- * each with its circuit and Pauli-sum Hamiltonian, run by ONE persistent
- * kernel captured in a hipGraph.  Plans use opts (NULL = defaults; a zero
+ * each with its circuit and Pauli-sum Hamiltonian, run by one hipGraph launch
+ * (a kernel per level: pass p of every state that has one).  Plans use opts (NULL = defaults; a zero
  * k_max/tile asks the autotuner).  State memory is library-owned. */
 qs_status qs_batch_create(int n_states, const int *n_qubits, const qs_gate *const *circuits,
                           const size_t *n_gates, const uint64_t *const *x, const uint64_t *const *z,

@@ -167,6 +167,7 @@ struct qs_plan_s {
     int dev_ready[2] = {0, 0};
     qs::BlockDev *d_blocks[2] = {nullptr, nullptr};
     void *d_pool[2] = {nullptr, nullptr};
+    size_t pool_bytes[2] = {0, 0};
     std::vector<qs::BlockDev> h_blocks[2];
     std::vector<uint8_t> pass_wide[2];  // pass needs the wide kernel variant
     // pool range of the pass's block operands staged in LDS (len 0 = none)
@@ -247,6 +248,8 @@ qs_status launch_pass(qs_state_s &s, const qs_plan_s &p, const HPass &pass, int6
 qs_status launch_norm_reduce(qs_state_s &s, uint64_t nparts, double *d_out_slots);
 qs_status launch_norm_full(qs_state_s &s, double *d_out_slots);
 qs_status ensure_partials(qs_state_s &s, size_t count);
+// whether a kernel's dynamic LDS starts at LDS address 0 (it declares no static LDS)
+bool dynamic_tile_at_zero(const void *fn);
 // kernels_expect.hip: Pauli-sum expectation, one read of the state per group
 // of terms whose high X parts span at most kExpMaxD dimensions
 constexpr int kExpMaxD = 9;            // span dimension of a group (coset = 2^D tiles)
@@ -287,6 +290,34 @@ struct ExpectPlan {
 // max_grid (0 = no limit) caps the workgroups of the launch
 qs_status expect_plan(int n, qs_dtype dt, const uint64_t *x, const uint64_t *z, size_t n_terms, ExpectPlan &out,
                       uint32_t max_grid = 0);
+// A batch's energies: every state is a job with its groups and terms (device
+// arrays, term 0 the identity); an item is per_item consecutive cosets of one
+// group, and writes one partial per term of the group at
+// part0 + term * chunks + chunk.
+struct ExpectJob {
+    uint64_t psi0;           // the state's first byte in the batch's amplitudes
+    uint64_t part0;
+    uint64_t group0, term0;  // first group and term (the kernels take the arrays as arguments,
+    uint64_t coeff0;         // so that wave-uniform reads of them are scalar); coeff of term 1
+    int32_t l, D, b, log_cosets;
+    uint32_t per_item, chunks, n_terms, pad;
+};
+struct ExpectItem {
+    uint32_t job, group, chunk, pad;
+};
+struct ExpectJobs {
+    const ExpectJob *jobs;
+    const ExpectGroup *groups;
+    const ExpectTerm *terms;
+    const double *coeff;
+    const void *amps;
+    double *parts;
+    int n_jobs;
+    const ExpectItem *items;     // n_full items of states that hold a full coset, then n_small of smaller ones
+    uint32_t n_full, n_small;
+};
+// energies receives one value per job
+void launch_expect_jobs(hipStream_t st, qs_dtype dt, const ExpectJobs &j, double *energies);
 size_t expect_scratch_bytes(const ExpectPlan &p);
 // d_scratch: expect_scratch_bytes(p) device bytes, 256-byte aligned; *d_out
 // receives the device address of the terms.size() results (term 0 = norm^2)

@@ -110,7 +110,8 @@ static_assert(kExpMaxTerms == 9, "add_to lists one case per accumulator");
 // Sum over this thread's pairs (j, j^x), j = ins0(t + m T, h) for m < NA/2, of
 // sign(j) Re(conj(psi[j^x]) psi[j]) (IMAG: Im), without the thread's own
 // sign parity(ins0(t, h) & z).  The LDS reads of H pairs are issued together.
-template <typename V, int T, int NA, bool GUARD, bool IMAG>
+// P64: the products of complex64 amplitudes in FP64 (exact), else in FP32.
+template <typename V, int T, int NA, bool GUARD, bool P64, bool IMAG>
 __device__ __forceinline__ double pair_sum(const V *L, uint32_t t, uint32_t size, const ExpectTerm &tm,
                                            uint32_t lane_j) {
     const char *Lb = (const char *)L;
@@ -134,7 +135,7 @@ __device__ __forceinline__ double pair_sum(const V *L, uint32_t t, uint32_t size
 #pragma unroll
         for (int i = 0; i < H; ++i) {
             double v;
-            if constexpr (sizeof(a[i].x) == 4) {
+            if constexpr (sizeof(a[i].x) == 4 && !P64) {
                 // complex64: the pair's part of conj(c) a in FP32 (one product and one
                 // fused multiply-add: relative error below 2^-23), accumulated in FP64
                 v = IMAG ? (double)__builtin_fmaf(c[i].x, a[i].y, -(c[i].y * a[i].x))
@@ -170,6 +171,99 @@ __device__ __forceinline__ double diag_sum(const V *L, uint32_t t, uint32_t size
         }
     }
     return P;
+}
+
+// ---- one coset: registers, LDS, terms ----------------------------------------
+//   V   cf2 (complex64) or cd2 (complex128)
+//   T   threads per workgroup
+//   NA  amplitudes each thread stages per coset
+//   GUARD  the coset may be smaller than T x NA (one-wave variant for small states)
+template <typename V, int NA>
+struct CosetRegs {
+    static constexpr int AV = LoadUnit<V>::amps;   // amplitudes per 16-byte load
+    static constexpr int NL = NA / AV;             // loads per thread and coset
+    typename LoadUnit<V>::T v[NL];
+};
+
+// registers <- coset number c of the group: load j of this thread holds
+// amplitudes q = (j T + t) AV + e, e < AV (one tile, since 2^l >= AV)
+template <typename V, int T, int NA, bool GUARD>
+__device__ __forceinline__ void coset_load(CosetRegs<V, NA> &r, const V *__restrict__ psi, const ExpectGroup &g,
+                                           uint32_t c, int D, int l, uint32_t size) {
+    using LV = typename LoadUnit<V>::T;
+    constexpr int AV = CosetRegs<V, NA>::AV;
+    const uint32_t t = threadIdx.x, lmask = (1u << l) - 1;
+    const uint32_t lane_v = coset_rep(g, c, D) ^ span_vec(g, (t * AV) >> l);
+    // amplitude index = ((lane_v ^ mv[j]) << l) | r = lane_idx ^ (mv[j] << l)
+    const uint64_t lane_idx = ((uint64_t)lane_v << l) | ((t * AV) & lmask);
+#pragma unroll
+    for (int j = 0; j < CosetRegs<V, NA>::NL; ++j) {
+        if (GUARD && ((uint32_t)j * T + t) * AV >= size) break;
+        r.v[j] = ld_stream((const LV *)(psi + (lane_idx ^ ((uint64_t)g.mv[j] << l))));
+    }
+}
+
+template <typename V, int T, int NA, bool GUARD>
+__device__ __forceinline__ void coset_put(V *L, const CosetRegs<V, NA> &r, uint32_t size) {
+    using LV = typename LoadUnit<V>::T;
+    const uint32_t t = threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < CosetRegs<V, NA>::NL; ++j) {
+        if (GUARD && ((uint32_t)j * T + t) * CosetRegs<V, NA>::AV >= size) break;
+        ((LV *)L)[j * T + t] = r.v[j];
+    }
+}
+
+// acc[k] += this thread's share of term k of the group over the staged coset
+// with representative rep
+template <typename V, int T, int NA, bool GUARD>
+__device__ __forceinline__ void coset_terms(const V *L, const ExpectGroup &g, const ExpectTerm *__restrict__ terms,
+                                            uint32_t rep, uint32_t size, double (&acc)[kExpMaxTerms]) {
+    const uint32_t t = threadIdx.x;
+#pragma unroll 1
+    for (int k = 0; k < g.nterms; ++k) {
+        const ExpectTerm &tm = terms[g.term0 + k];
+        const int sc = par32(rep & tm.zh);
+        double P = 0.0;
+        int lane_par;
+        if (tm.xloc == 0) {
+            lane_par = par32(t & tm.zloc);
+            P = diag_sum<V, T, NA, GUARD>(L, t, size, tm);
+        } else {
+            const int h = 31 - __clz(tm.xloc);
+            const uint32_t lane_j = ins0_32(t, h);
+            lane_par = par32(lane_j & tm.zloc);
+            P = tm.imag ? pair_sum<V, T, NA, GUARD, true, true>(L, t, size, tm, lane_j)
+                        : pair_sum<V, T, NA, GUARD, true, false>(L, t, size, tm, lane_j);
+        }
+        add_to(acc, k, (lane_par ^ sc) ? -P : P);
+    }
+}
+
+// out[k * stride] = sum over the workgroup of acc[k], k < nt, in a fixed order;
+// the accumulators restart at zero.  Begins behind the caller's barrier on
+// red's last readers and ends with one.
+template <int T>
+__device__ __forceinline__ void coset_flush(double (&acc)[kExpMaxTerms], int nt, double (&red)[kExpMaxTerms][T / 64],
+                                            double *__restrict__ out, uint64_t stride) {
+    const uint32_t t = threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < kExpMaxTerms; ++k) {
+        if (k < nt) {
+            double v = acc[k];
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+            if ((t & 63) == 0) red[k][t >> 6] = v;
+        }
+        acc[k] = 0.0;
+    }
+    __syncthreads();
+    for (int k = (int)t; k < nt; k += (int)T) {
+        double s = 0.0;
+        for (uint32_t i = 0; i < T / 64; ++i) s += red[k][i];
+        out[(uint64_t)k * stride] = s;
+    }
+    __syncthreads();
 }
 
 // One workgroup per (group, coset) item, persistent: workgroup w takes items
@@ -275,13 +369,91 @@ __global__ __launch_bounds__(T) void k_expect_coset(
                 const int h = 31 - __clz(tm.xloc);
                 const uint32_t lane_j = ins0_32(t, h);
                 lane_par = par32(lane_j & tm.zloc);
-                P = tm.imag ? pair_sum<V, T, NA, GUARD, true>(L, t, size, tm, lane_j)
-                            : pair_sum<V, T, NA, GUARD, false>(L, t, size, tm, lane_j);
+                P = tm.imag ? pair_sum<V, T, NA, GUARD, false, true>(L, t, size, tm, lane_j)
+                            : pair_sum<V, T, NA, GUARD, false, false>(L, t, size, tm, lane_j);
             }
             add_to(acc, k, (lane_par ^ sc) ? -P : P);
         }
     }
     if (g_cur >= 0) flush(g_cur);
+}
+
+// The same evaluation for many states at once (a batch's energies): one
+// workgroup per item = a run of consecutive cosets of one group of one state,
+// the next coset's amplitudes in registers while the current one is
+// evaluated; one partial per item and term.  Products are FP64 for either
+// dtype.  The batch read the state once per eight terms and term pair before
+// (one gather per term and amplitude): 64 states of 12..21 qubits with 200
+// terms each took 8 ms, grouped 2.2 ms; the FP64 conversions of complex64
+// amplitudes (32 per 8 pairs) and LDS reads bound it.  The tables are kernel
+// arguments with offsets per job: read through pointers held in the job
+// record they became per-lane generic loads, and the launch took 3.8 ms.
+template <typename V, int B, int T, int NA, bool GUARD>
+__global__ __launch_bounds__(T) void k_expect_jobs(const unsigned char *__restrict__ amps,
+                                                   const ExpectJob *__restrict__ jobs,
+                                                   const ExpectItem *__restrict__ items,
+                                                   const ExpectGroup *__restrict__ groups,
+                                                   const ExpectTerm *__restrict__ all_terms,
+                                                   double *__restrict__ parts) {
+    static_assert(T * NA == (1 << B), "threads x staged amplitudes = the largest coset");
+    __shared__ V L[1 << B];
+    __shared__ double red[kExpMaxTerms][T / 64];
+    const ExpectItem it = items[blockIdx.x];
+    const ExpectJob &job = jobs[it.job];
+    const V *psi = (const V *)(amps + job.psi0);
+    const int l = job.l, D = job.D;
+    const uint32_t size = 1u << job.b, cosets = 1u << job.log_cosets;
+    const ExpectGroup &g = groups[job.group0 + it.group];
+    const ExpectTerm *terms = all_terms + job.term0;
+    const uint32_t c0 = it.chunk * job.per_item;
+    const uint32_t c1 = c0 + job.per_item < cosets ? c0 + job.per_item : cosets;
+    double acc[kExpMaxTerms];
+#pragma unroll
+    for (int k = 0; k < kExpMaxTerms; ++k) acc[k] = 0.0;
+    CosetRegs<V, NA> pre;
+    coset_load<V, T, NA, GUARD>(pre, psi, g, c0, D, l, size);
+    for (uint32_t c = c0; c < c1; ++c) {
+        __syncthreads();   // the previous coset's terms are done with L
+        coset_put<V, T, NA, GUARD>(L, pre, size);
+        __syncthreads();
+        if (c + 1 < c1) coset_load<V, T, NA, GUARD>(pre, psi, g, c + 1, D, l, size);
+        coset_terms<V, T, NA, GUARD>(L, g, terms, coset_rep(g, c, D), size, acc);
+    }
+    coset_flush<T>(acc, g.nterms, red, parts + job.part0 + (uint64_t)g.term0 * job.chunks + it.chunk, job.chunks);
+}
+
+// Energy of every job's state from the partials of k_expect_jobs: one
+// workgroup per state, one wave per term (lanes stride the term's partials),
+// then the waves' sums in order.  Term 0 is the squared norm.
+constexpr int kJobEnergyThreads = 1024;
+__global__ __launch_bounds__(kJobEnergyThreads) void k_jobs_energy(const ExpectJob *__restrict__ jobs,
+                                                                   const ExpectTerm *__restrict__ terms,
+                                                                   const double *__restrict__ coeff,
+                                                                   const double *__restrict__ parts,
+                                                                   double *__restrict__ energies) {
+    constexpr int NW = kJobEnergyThreads / 64;
+    __shared__ double red[NW], nrm;
+    const ExpectJob &job = jobs[blockIdx.x];
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double e = 0.0;
+    for (uint32_t k = wave; k < job.n_terms; k += NW) {
+        double s = 0.0;
+        for (uint32_t c = lane; c < job.chunks; c += 64) s += parts[job.part0 + (uint64_t)k * job.chunks + c];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+        if (k == 0) {
+            if (lane == 0) nrm = s;
+        } else {
+            e = fma(coeff[job.coeff0 + k - 1] * terms[job.term0 + k].factor, s, e);
+        }
+    }
+    if (lane == 0) red[wave] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < NW; ++w) t += red[w];
+        energies[blockIdx.x] = t / nrm;
+    }
 }
 
 // out[k] = factor_k * sum of parts[w][k] over the workgroups w that had items
@@ -505,6 +677,25 @@ qs_status launch_expect(qs_state_s &s, const ExpectPlan &p, void *d_scratch, dou
     QS_HIP(hipGetLastError());
     *d_out = d_res;
     return QS_OK;
+}
+
+void launch_expect_jobs(hipStream_t st, qs_dtype dt, const ExpectJobs &j, double *energies) {
+    auto run = [&](auto kernel, int threads, const ExpectItem *items, uint32_t count) {
+        if (count)
+            hipLaunchKernelGGL(kernel, dim3(count), dim3(threads), 0, st, (const unsigned char *)j.amps, j.jobs, items,
+                               j.groups, j.terms, j.parts);
+    };
+    if (dt == QS_C64) {
+        run(k_expect_jobs<cf2, kExpCosetBits64, kExpThreads, kExpAmps64, false>, kExpThreads, j.items, j.n_full);
+        run(k_expect_jobs<cf2, 10, kExpSmallThreads, kExpAmps64, true>, kExpSmallThreads, j.items + j.n_full,
+            j.n_small);
+    } else {
+        run(k_expect_jobs<cd2, kExpCosetBits128, kExpThreads, kExpAmps128, false>, kExpThreads, j.items, j.n_full);
+        run(k_expect_jobs<cd2, 9, kExpSmallThreads, kExpAmps128, true>, kExpSmallThreads, j.items + j.n_full,
+            j.n_small);
+    }
+    hipLaunchKernelGGL(k_jobs_energy, dim3((unsigned)j.n_jobs), dim3(kJobEnergyThreads), 0, st, j.jobs, j.terms,
+                       j.coeff, j.parts, energies);
 }
 
 // ------------------------------------------------- library-held scratch

@@ -1004,6 +1004,8 @@ uint64_t resident_groups(const void *fn, int threads, size_t lds) {
     return (uint64_t)per_cu * (uint64_t)cus;
 }
 
+}  // namespace
+
 // A variant whose tile is the start of its dynamic LDS forms tile addresses
 // with OR and XOR, which needs the tile at LDS address 0 (the dynamic region
 // declares 128 KiB alignment): such a kernel must declare no static LDS.
@@ -1018,8 +1020,6 @@ bool dynamic_tile_at_zero(const void *fn) {
     seen.emplace_back(fn, ok);
     return ok;
 }
-
-}  // namespace
 
 int block_kind(const HBlock &b, int t, qs_dtype dt, std::vector<int> *dest, bool lds) {
     if (b.pauli) return BK_PAULI;
@@ -1164,6 +1164,7 @@ qs_status plan_upload_impl(qs_plan_s &p, qs_dtype dt, bool stage_lds) {
     if (pbytes)
         QS_HIP(hipMemcpy(p.d_pool[di], dt == QS_C64 ? (const void *)pool32.data() : (const void *)pool64.data(), pbytes,
                          hipMemcpyHostToDevice));
+    p.pool_bytes[di] = pbytes;
     p.dev_ready[di] = 1;
     return QS_OK;
 }

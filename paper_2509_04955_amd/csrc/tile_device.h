@@ -1,5 +1,5 @@
 // Device-side building blocks of a tile pass, shared by the single-state pass
-// kernel and the persistent batch kernel.  Internal to libqsim.
+// kernel and the batch kernel.  Internal to libqsim.
 //
 // A tile is 2^t amplitudes held in LDS; tile position j < c is global qubit j,
 // position c + i is the i-th "high" qubit of the pass.  Blocks (fused k-qubit

@@ -288,7 +288,7 @@ def qs_expect_pauli_sum_noalloc(h, x, z, coeff, with_terms: bool = False):
 
 
 class Batch:
-    """A batch of states run by one persistent kernel in a hipGraph
+    """A batch of states run by one hipGraph launch
     (qs_batch_create / qs_batch_run)."""
 
     def __init__(self, circuits, hams, o: qs_contract_opts | None = None, stream: int | None = None):

@@ -96,3 +96,22 @@ def test_batch_rejects_bad_input(Q):
     h = qsynth.random_pauli_sum(6, 3, seed=(1, 2))  # acts on qubit 5 of a 5-qubit state
     with pytest.raises(Q.QsimError):
         Q.Batch([c], [h], Q.opts(k_max=2, tile_qubits=5))
+
+
+@pytest.mark.parametrize("dtype,tol", [(0, 1e-6), (1, 1e-12)])
+def test_batch_item_and_coset_edges(Q, oracle, dtype, tol):
+    """Levels and energy items at their edges: one-qubit states, states just
+    below and at a full expectation coset (14 qubits complex64, 13 complex128),
+    and a pass of 2^13 four-qubit tiles, whose items hold several tiles.
+    Tolerances as for the uneven batch above."""
+    ns = (1, 2, 5, 12, 13, 14, 15, 17)
+    circuits = [qsynth.random_circuit(n, 40, seed=60 + n) for n in ns]
+    hams = [qsynth.random_pauli_sum(n, 1 + 5 * i, seed=(6, n)) for i, n in enumerate(ns)]
+    b = Q.Batch(circuits, hams, Q.opts(k_max=2, tile_qubits=4, low_qubits=2, dtype=dtype))
+    E = b.run()
+    assert np.array_equal(E, b.run())
+    for i, (c, h) in enumerate(zip(circuits, hams)):
+        psi, e = _oracle_energy(oracle, c, h)
+        assert abs(E[i] - e) <= tol * max(1, abs(e)), (i, c.n, E[i], e)
+        assert oracle.max_abs(psi, b.amplitudes(i)) <= (1e-5 if dtype == 0 else 1e-12)
+    b.close()
