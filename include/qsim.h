@@ -147,10 +147,13 @@ qs_status qs_state_copy_in(qs_state s, uint64_t offset, uint64_t count, const do
 qs_status qs_norm(qs_state s, double *out);
 
 /* ------------------------------------------------- plain gate-by-gate */
-/* Apply gates in program order, one HIP kernel sweep per gate (Algorithms 1
- * and 2; controlled gates touch only the control-1 half, Eq. 4).  The list
- * is validated before anything is launched: any bad gate -> QS_EINVAL and
- * the state is unchanged.  Asynchronous on the state's stream. */
+/* Apply gates as they are: no products of gates are formed, and gates that
+ * share a qubit keep their program order.  A single gate is one kernel sweep
+ * (Algorithms 1 and 2; controlled gates touch only the control-1 half, Eq. 4);
+ * the gates of a list share sweeps, each applied to tiles of the state in LDS
+ * while they are there.  The list is validated before anything is launched:
+ * any bad gate -> QS_EINVAL and the state is unchanged.  Asynchronous on the
+ * state's stream. */
 qs_status qs_apply_gates(qs_state s, const qs_gate *gates, size_t n_gates);
 
 /* The same circuit with staggered multi-gate parallelism (Section 3.3, the

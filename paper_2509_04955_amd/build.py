@@ -30,6 +30,7 @@ SOURCES = [
     "kernels_tile.hip",
     "kernels_expect.hip",
     "kernels_smgp.hip",
+    "kernels_gates.hip",
     "batch.hip",
     "mlp.hip",
     "autotune.cpp",

@@ -283,11 +283,7 @@ qs_status qs_apply_gates(qs_state s, const qs_gate *gates, size_t n_gates) {
     if (st != QS_OK) return st;
     st = materialize(*s);
     if (st != QS_OK) return st;
-    for (const HGate &g : hg) {
-        st = launch_plain(*s, g);
-        if (st != QS_OK) return st;
-    }
-    return QS_OK;
+    return launch_gates(*s, hg);
     QS_ABI_CATCH
 }
 

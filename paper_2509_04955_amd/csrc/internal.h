@@ -236,6 +236,8 @@ qs_status costmodel_predict_device(const float *features, int n_rows, float *out
 // kernels_plain.hip
 struct Mat2 { double re[4], im[4]; };
 qs_status launch_plain(qs_state_s &s, const HGate &g);
+// kernels_gates.hip: the gates in runs, each run one read and write of the state
+qs_status launch_gates(qs_state_s &s, const std::vector<HGate> &gates);
 // kernels_smgp.hip: the gates in DAG layers with staggered multi-gate launches
 qs_status launch_smgp(qs_state_s &s, const std::vector<HGate> &gates);
 qs_status launch_scale(qs_state_s &s, const double *d_scale);
@@ -250,6 +252,8 @@ qs_status launch_norm_full(qs_state_s &s, double *d_out_slots);
 qs_status ensure_partials(qs_state_s &s, size_t count);
 // whether a kernel's dynamic LDS starts at LDS address 0 (it declares no static LDS)
 bool dynamic_tile_at_zero(const void *fn);
+// raises a kernel's dynamic LDS limit where it is below `bytes` (kept per kernel)
+hipError_t set_dynamic_lds(const void *fn, size_t bytes);
 // kernels_expect.hip: Pauli-sum expectation, one read of the state per group
 // of terms whose high X parts span at most kExpMaxD dimensions
 constexpr int kExpMaxD = 9;            // span dimension of a group (coset = 2^D tiles)

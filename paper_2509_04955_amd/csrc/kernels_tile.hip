@@ -457,27 +457,11 @@ size_t lds_operand_budget(int t, qs_dtype dt) {
 // the real embedding (the three-product form would spill there).
 bool big_staged(int t, qs_dtype dt) { return dt == QS_C64 && t == 13 && big_tiles_enabled(); }
 
-// Raise a kernel's dynamic LDS limit once per (kernel, size).
 // Per-kernel caches of launch attributes, shared by every state: one lock
 // (a lookup per pass launch is negligible beside the pass).
 std::mutex &kernel_cache_lock() {
     static std::mutex m;
     return m;
-}
-
-void set_lds_limit(const void *fn, size_t bytes) {
-    static std::vector<std::pair<const void *, size_t>> done;
-    std::lock_guard<std::mutex> lock(kernel_cache_lock());
-    for (auto &d : done)
-        if (d.first == fn) {
-            if (bytes > d.second) {
-                (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-                d.second = bytes;
-            }
-            return;
-        }
-    (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    done.emplace_back(fn, bytes);
 }
 
 bool mfma_enabled() {
@@ -998,13 +982,25 @@ uint64_t resident_groups(const void *fn, int threads, size_t lds) {
         if (cus <= 0) cus = 256;
     }
     int per_cu = 0;
-    set_lds_limit(fn, lds);
+    (void)set_dynamic_lds(fn, lds);
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds);
     if (e != hipSuccess || per_cu < 1) per_cu = 1;
     return (uint64_t)per_cu * (uint64_t)cus;
 }
 
 }  // namespace
+
+hipError_t set_dynamic_lds(const void *fn, size_t bytes) {
+    static std::vector<std::pair<const void *, size_t>> done;
+    std::lock_guard<std::mutex> lock(kernel_cache_lock());
+    auto it = std::find_if(done.begin(), done.end(), [&](const auto &d) { return d.first == fn; });
+    if (it != done.end() && bytes <= it->second) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) return e;
+    if (it != done.end()) it->second = bytes;
+    else done.emplace_back(fn, bytes);
+    return hipSuccess;
+}
 
 // A variant whose tile is the start of its dynamic LDS forms tile addresses
 // with OR and XOR, which needs the tile at LDS address 0 (the dynamic region
