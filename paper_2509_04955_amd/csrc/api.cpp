@@ -404,20 +404,7 @@ qs_status qs_apply_plan(qs_state s, qs_plan p) {
         QS_CHECK(ps.t <= tcap, QS_EINVAL, "plan tile %d too large for this dtype", ps.t);
     qs_status st = plan_upload(*p, s->dtype);
     if (st != QS_OK) return st;
-    const bool renorm = p->opts.renorm != 0;
-    for (size_t i = 0; i < p->passes.size(); ++i) {
-        const HPass &ps = p->passes[i];
-        uint64_t nparts = 0;
-        st = launch_pass(*s, *p, ps, (int64_t)i, s->scale_pending, renorm, &nparts);
-        if (st != QS_OK) return st;
-        s->scale_pending = false;
-        if (renorm) {
-            st = launch_norm_reduce(*s, nparts, s->d_slots);
-            if (st != QS_OK) return st;
-            s->scale_pending = true;
-        }
-    }
-    return QS_OK;
+    return launch_plan(*s, *p);
 }
 
 qs_status qs_expect_pauli_sum(qs_state s, const uint64_t *x, const uint64_t *z, const double *coeff, size_t n_terms,

@@ -94,6 +94,7 @@ struct PassArgs {
     int32_t want_norm;      // write FP64 sum |a|^2 partial per tile
     int32_t cl_off;         // block operands staged in LDS: pool elements
     int32_t cl_len;         //   [cl_off, cl_off + cl_len), 0 = none
+    int32_t nsum;           // scale from the sum of this many norm partials (0: *scale)
 };
 
 // --------------------------------------------------------------- state
@@ -244,10 +245,11 @@ qs_status launch_scale(qs_state_s &s, const double *d_scale);
 qs_status launch_set_basis(qs_state_s &s, uint64_t index);
 qs_status launch_copy(void *dst, const void *src, uint64_t bytes, hipStream_t st);
 // kernels_tile.hip
-// nparts (optional) receives the number of FP64 norm partials the pass wrote
-qs_status launch_pass(qs_state_s &s, const qs_plan_s &p, const HPass &pass, int64_t pass_index, bool scale_in,
-                      bool want_norm, uint64_t *nparts = nullptr);
-qs_status launch_norm_reduce(qs_state_s &s, uint64_t nparts, double *d_out_slots);
+// one pass as it stands, without scale or norm
+qs_status launch_pass(qs_state_s &s, const qs_plan_s &p, const HPass &pass, int64_t pass_index);
+// every pass of an uploaded plan with its renormalisation
+qs_status launch_plan(qs_state_s &s, const qs_plan_s &p);
+qs_status launch_norm_reduce(qs_state_s &s, const double *parts, uint64_t nparts, double *d_out_slots);
 qs_status launch_norm_full(qs_state_s &s, double *d_out_slots);
 qs_status ensure_partials(qs_state_s &s, size_t count);
 // whether a kernel's dynamic LDS starts at LDS address 0 (it declares no static LDS)

@@ -136,7 +136,17 @@ constexpr int tile_waves() {
 // kTileAlign (block code then forms addresses with OR and XOR alone).
 constexpr size_t kRedBytes = 128 + 16;   // NT / 64 doubles for up to 1024 threads, two ticket slots
 
-template <typename R, bool WIDE, int NJ, bool CL, int NT = TT>
+//
+// ONE: a launch that gives every tile its own resident workgroup (states of up
+// to about 2^21 amplitudes).  Nothing is left to hand out or to prefetch, so
+// tile and workgroup share a number: no tickets (two dependent atomics on one
+// address by every workgroup before its first load) and no second read of the
+// tile in place of a next one.  Such a pass may also take the sum of the
+// previous pass's norm partials upon itself (pa.nsum of them, behind its tile
+// loads) instead of a reduction launch between the two: scale_in is then the
+// partials.  59 passes on 22 qubits complex64 (2^13 tiles): 45 -> 26 us a pass
+// with its norm; 10 passes on 19 qubits complex128: 45 -> 35 us.
+template <typename R, bool WIDE, int NJ, bool CL, int NT = TT, bool ONE = false>
 __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT>())) void k_tile_pass(
     typename AmpOf<R>::A *__restrict__ psi, uint64_t ntiles, PassArgs pa, const BlockDev *__restrict__ blocks,
     const R *__restrict__ pool, const double *__restrict__ scale_in, double *__restrict__ partials,
@@ -175,7 +185,7 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT>())) void k_til
         cst = reinterpret_cast<R *>(smem_raw + (size_t)tsize * sizeof(A) + kRedBytes);
     }
     const TileAligned tl{lds_addr(tile)};
-    const R sc = pa.apply_scale ? (R)(*scale_in) : (R)1;
+    R sc = !ONE && pa.apply_scale ? (R)(*scale_in) : (R)1;
     const uint32_t my_li = threadIdx.x * APV;
     const bool active = NJ > 0 || my_li < tsize;   // small tiles: fewer vectors than threads
     const uint64_t g_t = active ? tile_offset(my_li, pa) : 0;
@@ -200,6 +210,80 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT>())) void k_til
                 if (j0 + i < nj) lds_put(j0 + i, pre[i]);
         }
     };
+    auto norm_of = [](const V &v) -> double {
+        if constexpr (F32) return (double)v.x * v.x + (double)v.y * v.y + (double)v.z * v.z + (double)v.w * v.w;
+        else return v.x * v.x + v.y * v.y;
+    };
+    if constexpr (ONE) {
+        const uint64_t base = tile_base(blockIdx.x, pa);
+        constexpr int LD = NJ > 0 ? NJ : kPrefetch;   // vectors loaded at once
+        V v[LD];
+        auto load = [&](uint32_t j0) {
+#pragma unroll
+            for (int j = 0; j < LD; ++j)
+                if (NJ > 0 || (active && j0 + j < nj)) v[j] = *gaddr(base, j0 + j);
+        };
+        auto put = [&](uint32_t j0) {
+#pragma unroll
+            for (int j = 0; j < LD; ++j)
+                if (NJ > 0 || (active && j0 + j < nj)) lds_put(j0 + j, v[j]);
+        };
+        load(0);
+        if constexpr (CL) {
+            constexpr int EPV = 16 / sizeof(R);
+            for (int i = threadIdx.x * EPV; i < pa.cl_len; i += NT * EPV)
+                *reinterpret_cast<V *>(cst + i) = *reinterpret_cast<const V *>(pool + pa.cl_off + i);
+        }
+        if (pa.apply_scale) {
+            if (pa.nsum) {
+                double s = 0;
+                for (int i = threadIdx.x; i < pa.nsum; i += NT) s += scale_in[i];
+                red[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)] = wave_sum_f64(s);
+                __syncthreads();
+                double N = 0;
+#pragma unroll
+                for (int w = 0; w < NT / 64; ++w) N += red[w];
+                sc = (R)(N > 0 ? 1.0 / sqrt(N) : 1.0);
+            } else {
+                sc = (R)(*scale_in);
+            }
+        }
+        put(0);
+        for (uint32_t j0 = LD; j0 < nj; j0 += LD) {
+            load(j0);
+            put(j0);
+        }
+        __syncthreads();
+        for (int b = 0; b < pa.nblocks; ++b) {
+            if (blocks[pa.block0 + b].kind == BK_SKIP) continue;   // folded into a group (uniform)
+            apply_block<R, WIDE, CL, NT>(tl, T, blocks + pa.block0 + b, pool, base, cst, pa.cl_off);
+            __syncthreads();
+        }
+        double nacc = 0.0;
+        for (uint32_t j0 = 0; j0 < nj; j0 += LD) {
+#pragma unroll
+            for (int j = 0; j < LD; ++j)
+                if (NJ > 0 || (active && j0 + j < nj))
+                    v[j] = *tl.template at<const V>(h_t, sw((j0 + j) * NT * APV) * (uint32_t)sizeof(A));
+#pragma unroll
+            for (int j = 0; j < LD; ++j)
+                if (NJ > 0 || (active && j0 + j < nj)) {
+                    *gaddr(base, j0 + j) = v[j];
+                    nacc += norm_of(v[j]);
+                }
+        }
+        if (pa.want_norm) {
+            red[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)] = wave_sum_f64(nacc);
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                double s = 0;
+#pragma unroll
+                for (int w = 0; w < NT / 64; ++w) s += red[w];
+                partials[blockIdx.x] = s;
+            }
+        }
+        return;
+    }
     // Tiles are handed out in ascending order by a ticket counter (the state's,
     // advanced by ntiles + grid per pass: every workgroup draws until it gets
     // a ticket past the last tile), so a workgroup that runs faster than its
@@ -272,10 +356,6 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT>())) void k_til
         }
         // ---- store + FP64 norm partial ----
         double nacc = 0.0;
-        auto norm_of = [](const V &v) -> double {
-            if constexpr (F32) return (double)v.x * v.x + (double)v.y * v.y + (double)v.z * v.z + (double)v.w * v.w;
-            else return v.x * v.x + v.y * v.y;
-        };
         if constexpr (NJ > 0) {
             // every LDS read issued before the first store: one wait chain
             // instead of a read latency per stored vector
@@ -387,52 +467,53 @@ using TileKernel = void (*)(typename AmpOf<R>::A *, uint64_t, PassArgs, const Bl
                             double *, unsigned long long *, unsigned long long);
 
 // Kernel variant for a pass: register footprint (wide), LDS-staged operands
-// (cl) and, for the narrow variant, the compile-time vector count.
-template <typename R>
+// (cl), a workgroup per tile (ONE) and, for the narrow variant and wide ONE
+// passes of complex128, the compile-time vector count.
+template <typename R, bool ONE>
 TileKernel<R> pick_tile_kernel(bool wide, int t, bool cl, int &threads, bool &static_tile) {
     constexpr int APV = sizeof(R) == 4 ? 2 : 1;
     const int vpt = (1 << t) / (TT * APV);   // 16-byte vectors per thread
     threads = TT;
     static_tile = false;
-    if (wide) return k_tile_pass<R, true, 0, false>;
+    if (wide) return k_tile_pass<R, true, 0, false, TT, ONE>;
     if constexpr (sizeof(R) == 4) {
         // unstaged 2^13 / 2^14 tiles: more threads per workgroup, 8 vectors each
         if (!cl && big_tiles_enabled()) {
             static_tile = t == 13 || t == 14;
             if (t == 13) {
                 threads = 512;
-                return k_tile_pass<R, false, 8, false, 512>;
+                return k_tile_pass<R, false, 8, false, 512, ONE>;
             }
             if (t == 14) {
                 threads = 1024;
-                return k_tile_pass<R, false, 8, false, 1024>;
+                return k_tile_pass<R, false, 8, false, 1024, ONE>;
             }
         }
         if (cl && big_tiles_enabled() && t == 13) {
             threads = 512;
-            return k_tile_pass<R, false, 8, true, 512>;
+            return k_tile_pass<R, false, 8, true, 512, ONE>;
         }
 
     }
     if ((1 << t) == vpt * TT * APV) {
         if (cl) {
             if constexpr (sizeof(R) == 4) {
-                if (vpt == 4) return k_tile_pass<R, false, 4, true>;
-                if (vpt == 8) return k_tile_pass<R, false, 8, true>;
-                if (vpt == 16) return k_tile_pass<R, false, 16, true>;
+                if (vpt == 4) return k_tile_pass<R, false, 4, true, TT, ONE>;
+                if (vpt == 8) return k_tile_pass<R, false, 8, true, TT, ONE>;
+                if (vpt == 16) return k_tile_pass<R, false, 16, true, TT, ONE>;
             } else {
-                if (vpt == 8) return k_tile_pass<R, false, 8, true>;
-                if (vpt == 16) return k_tile_pass<R, false, 16, true>;
+                if (vpt == 8) return k_tile_pass<R, false, 8, true, TT, ONE>;
+                if (vpt == 16) return k_tile_pass<R, false, 16, true, TT, ONE>;
             }
         }
         static_tile = vpt == 1 || vpt == 2 || vpt == 4 || vpt == 8 || vpt == 16;
-        if (vpt == 1) return k_tile_pass<R, false, 1, false>;
-        if (vpt == 2) return k_tile_pass<R, false, 2, false>;
-        if (vpt == 4) return k_tile_pass<R, false, 4, false>;
-        if (vpt == 8) return k_tile_pass<R, false, 8, false>;
-        if (vpt == 16) return k_tile_pass<R, false, 16, false>;
+        if (vpt == 1) return k_tile_pass<R, false, 1, false, TT, ONE>;
+        if (vpt == 2) return k_tile_pass<R, false, 2, false, TT, ONE>;
+        if (vpt == 4) return k_tile_pass<R, false, 4, false, TT, ONE>;
+        if (vpt == 8) return k_tile_pass<R, false, 8, false, TT, ONE>;
+        if (vpt == 16) return k_tile_pass<R, false, 16, false, TT, ONE>;
     }
-    return k_tile_pass<R, false, 0, false>;
+    return k_tile_pass<R, false, 0, false, TT, ONE>;
 }
 
 // LDS bytes a pass may use for staged operands: what is left of the CU's LDS
@@ -971,21 +1052,26 @@ size_t pass_operand_bytes(const std::vector<HBlock> &blocks, const HPass &ps, qs
     return b;
 }
 
-// Workgroups of a tile kernel resident at once on the current device.
+// Workgroups of a tile kernel resident at once on the current device (one
+// query per kernel and LDS size; the devices of a process are alike).
 uint64_t resident_groups(const void *fn, int threads, size_t lds) {
-    static int cus = 0;
-    if (!cus) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            cus = prop.multiProcessorCount;
-        if (cus <= 0) cus = 256;
-    }
-    int per_cu = 0;
-    (void)set_dynamic_lds(fn, lds);
+    struct Entry {
+        const void *fn;
+        size_t lds;
+        uint64_t groups;
+    };
+    static std::vector<Entry> seen;
+    std::lock_guard<std::mutex> lock(kernel_cache_lock());
+    for (const Entry &e : seen)
+        if (e.fn == fn && e.lds == lds) return e.groups;
+    int dev = 0, cus = 0, per_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds);
     if (e != hipSuccess || per_cu < 1) per_cu = 1;
-    return (uint64_t)per_cu * (uint64_t)cus;
+    seen.push_back({fn, lds, (uint64_t)per_cu * (uint64_t)cus});
+    return seen.back().groups;
 }
 
 }  // namespace
@@ -1179,8 +1265,59 @@ qs_status ensure_partials(qs_state_s &s, size_t count) {
     return QS_OK;
 }
 
-qs_status launch_pass(qs_state_s &s, const qs_plan_s &p, const HPass &ps, int64_t pass_index, bool scale_in,
-                      bool want_norm, uint64_t *nparts) {
+namespace {
+
+// The launch of a pass: variant, grid and LDS.
+struct PassLaunch {
+    TileKernel<float> k32 = nullptr;
+    TileKernel<double> k64 = nullptr;
+    int threads = TT;
+    bool one = false;        // a workgroup per tile
+    size_t lds = 0;
+    uint64_t ntiles = 0;
+    unsigned grid = 0;
+};
+
+qs_status pass_launch(const qs_state_s &s, const qs_plan_s &p, const HPass &ps, int64_t pass_index, PassLaunch &L) {
+    const int di = s.dtype == QS_C64 ? 0 : 1;
+    const bool wide = p.pass_wide[di][pass_index] != 0, cl = p.pass_cl_len[di][pass_index] > 0;
+    const size_t amp = s.dtype == QS_C64 ? 8 : 16;
+    L.ntiles = 1ull << (s.n - ps.t);
+    for (const bool one : {true, false}) {
+        bool static_tile = false;
+        L.k32 = nullptr;
+        L.k64 = nullptr;
+        if (s.dtype == QS_C64)
+            L.k32 = one ? pick_tile_kernel<float, true>(wide, ps.t, cl, L.threads, static_tile)
+                        : pick_tile_kernel<float, false>(wide, ps.t, cl, L.threads, static_tile);
+        else
+            L.k64 = one ? pick_tile_kernel<double, true>(wide, ps.t, cl, L.threads, static_tile)
+                        : pick_tile_kernel<double, false>(wide, ps.t, cl, L.threads, static_tile);
+        // dynamic LDS: none for the static-tile variants, else tile + norm slots + staged operands
+        L.lds = static_tile ? 0
+                            : (amp << ps.t) + kRedBytes +
+                                  (size_t)p.pass_cl_len[di][pass_index] * (s.dtype == QS_C64 ? 4 : 8);
+        const void *fn = L.k32 ? reinterpret_cast<const void *>(L.k32) : reinterpret_cast<const void *>(L.k64);
+        QS_CHECK(static_tile || dynamic_tile_at_zero(fn), QS_EDEVICE,
+                 "tile kernel variant declares static LDS: its dynamic tile would not sit at LDS address 0");
+        QS_HIP(set_dynamic_lds(fn, L.lds));
+        const uint64_t resident = resident_groups(fn, L.threads, L.lds);
+        L.one = one;
+        // persistent grid: as many workgroups as fit on the device at once, each
+        // with the next tile's loads in flight while the current one is processed
+        L.grid = (unsigned)std::min<uint64_t>(L.ntiles, std::min<uint64_t>(resident, kMaxTileGrid));
+        if (L.grid == L.ntiles) break;   // each tile has its workgroup: the ONE variant
+    }
+    return QS_OK;
+}
+
+// Norm partials a pass may leave to the next pass to sum (each of its
+// workgroups reads them all): up to 2^11 they cost it about 1 us behind its
+// tile loads, where a reduction launch costs 5 us.
+constexpr uint64_t kMaxNextSum = 2048;
+
+qs_status run_pass(qs_state_s &s, const qs_plan_s &p, const HPass &ps, const PassLaunch &L, int64_t pass_index,
+                   bool scale_in, bool want_norm, const double *parts_in, uint64_t nsum, double *parts_out) {
     const int di = s.dtype == QS_C64 ? 0 : 1;
     PassArgs pa;
     std::memset(&pa, 0, sizeof pa);
@@ -1193,55 +1330,78 @@ qs_status launch_pass(qs_state_s &s, const qs_plan_s &p, const HPass &ps, int64_
     pa.want_norm = want_norm ? 1 : 0;
     pa.cl_off = p.pass_cl_off[di][pass_index];
     pa.cl_len = p.pass_cl_len[di][pass_index];
-    const bool cl = pa.cl_len > 0;
-    const uint64_t ntiles = 1ull << (s.n - ps.t);
-    // persistent grid: as many workgroups as fit on the device at once, each
-    // walking tiles blockIdx.x, blockIdx.x + grid, ... with the next tile's
-    // loads in flight while the current one is processed
-    const bool wide = p.pass_wide[di][pass_index] != 0;
-    const size_t amp = s.dtype == QS_C64 ? 8 : 16;
-    int threads = TT;
-    bool static_tile = false;
-    TileKernel<float> k32 = nullptr;
-    TileKernel<double> k64 = nullptr;
-    if (s.dtype == QS_C64) k32 = pick_tile_kernel<float>(wide, ps.t, cl, threads, static_tile);
-    else k64 = pick_tile_kernel<double>(wide, ps.t, cl, threads, static_tile);
-    // dynamic LDS: none for the static-tile variants, else tile + norm slots + staged operands
-    const size_t lds = static_tile ? 0 : (amp << ps.t) + kRedBytes + (size_t)pa.cl_len * (s.dtype == QS_C64 ? 4 : 8);
-    const void *fn = k32 ? reinterpret_cast<const void *>(k32) : reinterpret_cast<const void *>(k64);
-    QS_CHECK(static_tile || dynamic_tile_at_zero(fn), QS_EDEVICE,
-             "tile kernel variant declares static LDS: its dynamic tile would not sit at LDS address 0");
-    const uint64_t resident = resident_groups(fn, threads, lds);
-    const dim3 grid((unsigned)std::min<uint64_t>(ntiles, std::min<uint64_t>(resident, kMaxTileGrid)));
-    if (want_norm) {
-        qs_status st = ensure_partials(s, ntiles);
-        if (st != QS_OK) return st;
+    pa.nsum = (int32_t)nsum;
+    const double *scale = nsum ? parts_in : s.d_slots + 1;
+    const double S = std::ldexp((double)(s.dtype == QS_C64 ? 8 : 16), s.n);
+    if (prof_on()) {
+        double flops = 0;
+        for (int64_t b = ps.block0; b < ps.block0 + ps.nblocks; ++b)
+            flops += block_flops_per_amp(p.h_blocks[di][b]) * std::ldexp(1.0, s.n);
+        prof_begin(s.stream, QS_PROF_TILE, 2 * S, flops);
     }
-    if (nparts) *nparts = ntiles;   // one norm partial per tile
-    const double S = std::ldexp((double)amp, s.n);
-    double flops = 0;
-    for (int64_t b = ps.block0; b < ps.block0 + ps.nblocks; ++b)
-        flops += block_flops_per_amp(p.h_blocks[di][b]) * std::ldexp(1.0, s.n);
-    prof_begin(s.stream, QS_PROF_TILE, 2 * S, flops);
     unsigned long long *tickets = reinterpret_cast<unsigned long long *>(s.d_slots + kSlotTickets);
-    if (s.dtype == QS_C64)
-        hipLaunchKernelGGL(k32, grid, dim3(threads), lds, s.stream, (float2 *)s.amp, ntiles,
-                           pa, p.d_blocks[di], (const float *)p.d_pool[di], s.d_slots + 1, s.d_partials, tickets,
+    if (L.k32)
+        hipLaunchKernelGGL(L.k32, dim3(L.grid), dim3(L.threads), L.lds, s.stream, (float2 *)s.amp, L.ntiles, pa,
+                           p.d_blocks[di], (const float *)p.d_pool[di], scale, parts_out, tickets,
                            (unsigned long long)s.tickets);
     else
-        hipLaunchKernelGGL(k64, grid, dim3(threads), lds, s.stream, (double2 *)s.amp,
-                           ntiles, pa, p.d_blocks[di], (const double *)p.d_pool[di], s.d_slots + 1, s.d_partials,
-                           tickets, (unsigned long long)s.tickets);
+        hipLaunchKernelGGL(L.k64, dim3(L.grid), dim3(L.threads), L.lds, s.stream, (double2 *)s.amp, L.ntiles, pa,
+                           p.d_blocks[di], (const double *)p.d_pool[di], scale, parts_out, tickets,
+                           (unsigned long long)s.tickets);
     prof_end(s.stream);
     QS_HIP(hipGetLastError());
     // every tile's ticket plus one past the end per workgroup
-    s.tickets += ntiles + grid.x;
+    if (!L.one) s.tickets += L.ntiles + L.grid;
     return QS_OK;
 }
 
-qs_status launch_norm_reduce(qs_state_s &s, uint64_t nparts, double *d_out_slots) {
+}  // namespace
+
+qs_status launch_pass(qs_state_s &s, const qs_plan_s &p, const HPass &ps, int64_t pass_index) {
+    PassLaunch L;
+    const qs_status st = pass_launch(s, p, ps, pass_index, L);
+    if (st != QS_OK) return st;
+    return run_pass(s, p, ps, L, pass_index, false, false, nullptr, 0, nullptr);
+}
+
+qs_status launch_plan(qs_state_s &s, const qs_plan_s &p) {
+    const bool renorm = p.opts.renorm != 0;
+    std::vector<PassLaunch> launches(p.passes.size());
+    uint64_t most = 0;
+    for (size_t i = 0; i < p.passes.size(); ++i) {
+        const qs_status st = pass_launch(s, p, p.passes[i], (int64_t)i, launches[i]);
+        if (st != QS_OK) return st;
+        most = std::max(most, launches[i].ntiles);
+    }
+    if (renorm) {
+        // two sets of partials: a pass may read the previous pass's while it writes its own
+        const qs_status st = ensure_partials(s, 2 * most);
+        if (st != QS_OK) return st;
+    }
+    uint64_t nsum = 0;   // partials the next pass sums itself
+    for (size_t i = 0; i < p.passes.size(); ++i) {
+        double *out = s.d_partials + (i & 1) * most, *in = s.d_partials + (~i & 1) * most;
+        const uint64_t n = launches[i].ntiles;
+        qs_status st = run_pass(s, p, p.passes[i], launches[i], (int64_t)i, s.scale_pending || nsum, renorm, in, nsum,
+                                out);
+        if (st != QS_OK) return st;
+        s.scale_pending = false;
+        nsum = 0;
+        if (!renorm) continue;
+        if (i + 1 < p.passes.size() && launches[i + 1].one && n <= kMaxNextSum) {
+            nsum = n;
+            continue;
+        }
+        st = launch_norm_reduce(s, out, n, s.d_slots);
+        if (st != QS_OK) return st;
+        s.scale_pending = true;
+    }
+    return QS_OK;
+}
+
+qs_status launch_norm_reduce(qs_state_s &s, const double *parts, uint64_t nparts, double *d_out_slots) {
     prof_begin(s.stream, QS_PROF_REDUCE, 8.0 * nparts, nparts);
-    hipLaunchKernelGGL(k_norm_reduce, dim3(1), dim3(1024), 0, s.stream, s.d_partials, nparts, d_out_slots);
+    hipLaunchKernelGGL(k_norm_reduce, dim3(1), dim3(1024), 0, s.stream, parts, nparts, d_out_slots);
     prof_end(s.stream);
     QS_HIP(hipGetLastError());
     return QS_OK;
@@ -1260,7 +1420,7 @@ qs_status launch_norm_full(qs_state_s &s, double *d_out_slots) {
         hipLaunchKernelGGL(k_norm_parts<double2>, dim3((unsigned)nwg), dim3(256), 0, s.stream, (const double2 *)s.amp,
                            namps, chunk, s.d_partials);
     QS_HIP(hipGetLastError());
-    return launch_norm_reduce(s, nwg, d_out_slots);
+    return launch_norm_reduce(s, s.d_partials, nwg, d_out_slots);
 }
 
 }  // namespace qs

@@ -351,10 +351,10 @@ qs_status qs_plan_time_passes(qs_plan p, qs_dtype dtype, int reps, double *us_ou
     hipEventCreate(&e1);
     std::vector<float> t(reps);
     for (size_t i = 0; st == QS_OK && i < p->passes.size(); ++i) {
-        st = launch_pass(*s, *p, p->passes[i], (int64_t)i, false, false);  // warm
+        st = launch_pass(*s, *p, p->passes[i], (int64_t)i);  // warm
         for (int r = 0; st == QS_OK && r < reps; ++r) {
             hipEventRecord(e0, nullptr);
-            st = launch_pass(*s, *p, p->passes[i], (int64_t)i, false, false);
+            st = launch_pass(*s, *p, p->passes[i], (int64_t)i);
             hipEventRecord(e1, nullptr);
             if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&t[r], e0, e1) != hipSuccess) {
                 set_error("pass timing failed");
