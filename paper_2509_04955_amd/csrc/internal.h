@@ -221,7 +221,6 @@ void pauli_block_matrix(HBlock &b);
 std::vector<PauliWindow> pauli_windows(const std::vector<HGate> &gates, int k_max, int max_x_weight);
 void pauli_contract(const std::vector<HGate> &gates, int n, int k_max, const std::vector<PauliWindow> &win,
                     std::vector<HBlock> &blocks, bool commute = false);
-int default_tile(qs_dtype dt);
 // learned.cpp: features of one pass (kNumFeatures floats) and the learned
 // per-window partition
 constexpr int kNumFeatures = 17;

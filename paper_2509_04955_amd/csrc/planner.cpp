@@ -27,7 +27,43 @@
 
 namespace qs {
 
-int default_tile(qs_dtype dt) { return dt == QS_C128 ? 12 : 13; }
+namespace {
+
+// Tile qubits and fixed low qubits where the caller leaves them open, for n
+// qubits and blocks of up to k.  Geometric means over ansatz, random, UCC and
+// Fourier circuits, us per plan, against tiles of 2^13 (complex64) or 2^12
+// amplitudes with 6 low qubits:
+//   * 12..18 qubits: a pass is a few small workgroups in flight, and smaller
+//     tiles spread it over more CUs; states of this size stay in the caches, so
+//     short runs cost nothing (14 qubits complex64: 66 against 149 us for an
+//     ansatz of four layers; 16 qubits complex128: 126 against 239);
+//   * 19..22: the smallest tiles that still give every CU one or two
+//     (20 qubits complex64: 200 against 260; complex128 as noted below);
+//   * above: as many qubits as the LDS allows, fewest passes, and runs of a
+//     cache line (24 qubits complex64: 1700 against 2000).  Complex128 blocks
+//     of four and five qubits are held back by waves, not by passes: smaller
+//     tiles (24 qubits, k 5: 4.1 against 6.3 ms, 26 qubits: 18.7 against 25.6;
+//     k 3 is fastest at 2^12: 6.2 against 7.1 ms).
+// One tile holds states of up to 11 qubits (11 qubits: 44 us against 55 us in
+// two tiles).
+void auto_shape(int n, qs_dtype dt, int k, int &t, int &low) {
+    if (n <= 11) {
+        t = 11;
+        low = 6;
+    } else if (n <= (dt == QS_C64 ? 16 : 18)) {
+        t = 10;
+        low = 2;
+    } else if (dt == QS_C64) {
+        t = n <= 20 ? 11 : 13;
+        low = n <= 20 ? 3 : 4;
+    } else {
+        // 20 qubits, k 5: 352 us at 2^12 against 390; k 2..4: 262..334 against 235..295 at 2^11
+        t = n == 19 || (n == 20 && k < 5) || (n >= 23 && k >= 4) ? 11 : 12;
+        low = n >= 23 && k >= 5 ? 5 : 3;
+    }
+}
+
+}  // namespace
 
 namespace {
 
@@ -355,11 +391,13 @@ qs_status build_plan(qs_plan_s &p) {
     const int kcap = dt == QS_C128 ? kMaxK128 : kMaxK;
     if (o.k_max == 0) o.k_max = 5;
     QS_CHECK(o.k_max >= 1 && o.k_max <= kcap, QS_EINVAL, "k_max %d outside 1..%d", o.k_max, kcap);
-    if (o.tile_qubits == 0) o.tile_qubits = default_tile(dt);
+    int auto_t, auto_low;
+    auto_shape(p.n, dt, o.k_max, auto_t, auto_low);
+    if (o.tile_qubits == 0) o.tile_qubits = o.low_qubits > auto_t ? (dt == QS_C128 ? 12 : 13) : auto_t;
     const int tcap = dt == QS_C128 ? kMaxTile128 : kMaxTile;
     QS_CHECK(o.tile_qubits >= 2 && o.tile_qubits <= tcap, QS_EINVAL, "tile_qubits %d outside 2..%d",
              o.tile_qubits, tcap);
-    if (o.low_qubits == 0) o.low_qubits = std::min(6, o.tile_qubits);
+    if (o.low_qubits == 0) o.low_qubits = std::min(auto_low, o.tile_qubits);
     QS_CHECK(o.low_qubits >= 1 && o.low_qubits <= o.tile_qubits, QS_EINVAL, "low_qubits %d invalid",
              o.low_qubits);
     const int t = std::min(o.tile_qubits, p.n);
