@@ -60,10 +60,8 @@ void prof_end(hipStream_t st) {
 using namespace qs;
 
 qs_plan_s::~qs_plan_s() {
-    for (int i = 0; i < 2; ++i) {
-        if (d_blocks[i]) hipFree(d_blocks[i]);
+    for (int i = 0; i < 2; ++i)
         if (d_pool[i]) hipFree(d_pool[i]);
-    }
 }
 
 namespace {
@@ -117,10 +115,38 @@ qs_status check_expect_args(qs_state s, const uint64_t *x, const uint64_t *z, co
 // unnormalised terms, res[0] the squared norm.  Synchronises the stream.
 qs_status run_expect(qs_state_s &s, const ExpectPlan &plan, void *d_scr, std::vector<double> &res) {
     double *d_res = nullptr;
-    qs_status st = launch_expect(s, plan, d_scr, &d_res);
+    qs_status st = launch_expect(s, plan, d_scr, nullptr, &d_res);
     if (st != QS_OK) return st;
     QS_HIP(hipMemcpyAsync(res.data(), d_res, res.size() * sizeof(double), hipMemcpyDeviceToHost, s.stream));
     QS_HIP(hipStreamSynchronize(s.stream));
+    return QS_OK;
+}
+
+// the same in the state's own workspace
+qs_status run_expect_kept(qs_state_s &s, const ExpectPlan &plan, std::vector<double> &res) {
+    // every call ends synchronised: nothing on the stream uses the buffers now
+    const size_t need = expect_scratch_bytes(plan), host = expect_host_bytes(plan);
+    if (s.expect_cap < need) {
+        if (s.d_expect) QS_HIP(hipFree(s.d_expect));
+        s.d_expect = nullptr;
+        s.expect_cap = 0;
+        QS_HIP(hipMalloc(&s.d_expect, need));
+        s.expect_cap = need;
+    }
+    if (s.expect_host_cap < host) {
+        if (s.h_expect) QS_HIP(hipHostFree(s.h_expect));
+        s.h_expect = nullptr;
+        s.expect_host_cap = 0;
+        QS_HIP(hipHostMalloc(&s.h_expect, host, hipHostMallocDefault));
+        s.expect_host_cap = host;
+    }
+    double *out = nullptr;
+    const qs_status st = launch_expect(s, plan, s.d_expect, s.h_expect, &out);
+    // after a failure too: work may be queued on the buffers
+    const hipError_t e = hipStreamSynchronize(s.stream);
+    if (st != QS_OK) return st;
+    if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize(expectation)");
+    std::copy_n(out, res.size(), res.begin());
     return QS_OK;
 }
 
@@ -200,6 +226,8 @@ qs_status qs_state_destroy(qs_state s) {
     if (s->owned && s->amp) hipFree(s->amp);
     if (s->d_slots) hipFree(s->d_slots);
     if (s->d_partials) hipFree(s->d_partials);
+    if (s->d_expect) hipFree(s->d_expect);
+    if (s->h_expect) hipHostFree(s->h_expect);
     delete s;
     return QS_OK;
 }
@@ -414,17 +442,14 @@ qs_status qs_expect_pauli_sum(qs_state s, const uint64_t *x, const uint64_t *z, 
     if (st != QS_OK) return st;
     std::vector<double> terms(n_terms);
     double nrm = 0;
-    // launches of at most kExpTermsPerLaunch terms, each with its own scratch
+    // launches of at most kExpTermsPerLaunch terms
     for (size_t k0 = 0; k0 < n_terms; k0 += kExpTermsPerLaunch) {
         const size_t cnt = std::min(kExpTermsPerLaunch, n_terms - k0);
         ExpectPlan plan;
         st = expect_plan(s->n, s->dtype, x + k0, z + k0, cnt, plan);
         if (st != QS_OK) return st;
-        void *d_scr = nullptr;
-        QS_HIP(hipMalloc(&d_scr, expect_scratch_bytes(plan)));
         std::vector<double> res(plan.terms.size());
-        st = run_expect(*s, plan, d_scr, res);
-        hipFree(d_scr);
+        st = run_expect_kept(*s, plan, res);
         if (st != QS_OK) return st;
         if (k0 == 0) nrm = res[0];   // squared norm of the stored amplitudes (a pending scale cancels)
         std::copy(res.begin() + 1, res.end(), terms.begin() + k0);

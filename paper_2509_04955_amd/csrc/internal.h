@@ -118,6 +118,13 @@ struct qs_state_s {
     double *d_partials = nullptr;
     size_t partials_cap = 0;
     bool scale_pending = false;
+    // expectation workspace, kept between calls and grown to the largest (at
+    // most 4096 terms per launch: about 10 MB): device tables and partials,
+    // pinned host memory for the tables on their way and the results
+    void *d_expect = nullptr;
+    size_t expect_cap = 0;
+    void *h_expect = nullptr;
+    size_t expect_host_cap = 0;
 };
 
 namespace qs {
@@ -166,7 +173,7 @@ struct qs_plan_s {
     std::vector<qs::HPass> passes;
     // device copies (built on first use per dtype)
     int dev_ready[2] = {0, 0};
-    qs::BlockDev *d_blocks[2] = {nullptr, nullptr};
+    qs::BlockDev *d_blocks[2] = {nullptr, nullptr};   // behind the operands, in d_pool's allocation
     void *d_pool[2] = {nullptr, nullptr};
     size_t pool_bytes[2] = {0, 0};
     std::vector<qs::BlockDev> h_blocks[2];
@@ -324,9 +331,13 @@ struct ExpectJobs {
 // energies receives one value per job
 void launch_expect_jobs(hipStream_t st, qs_dtype dt, const ExpectJobs &j, double *energies);
 size_t expect_scratch_bytes(const ExpectPlan &p);
+// pinned host bytes of a launch: a copy of the tables, then the results
+size_t expect_host_bytes(const ExpectPlan &p);
 // d_scratch: expect_scratch_bytes(p) device bytes, 256-byte aligned; *d_out
-// receives the device address of the terms.size() results (term 0 = norm^2)
-qs_status launch_expect(qs_state_s &s, const ExpectPlan &p, void *d_scratch, double **d_out);
+// receives the address of the terms.size() results (term 0 = norm^2): in
+// h_pinned (expect_host_bytes(p) pinned bytes, valid once the stream is
+// synchronised) where that is given, else in d_scratch
+qs_status launch_expect(qs_state_s &s, const ExpectPlan &p, void *d_scratch, void *h_pinned, double **out);
 // the library-held scratch of the no-allocation expectation (kernels_expect.hip):
 // its device address on the current device, taken once per device; need
 // beyond its size gives QS_ERANGE.  noalloc_lock serialises its users.

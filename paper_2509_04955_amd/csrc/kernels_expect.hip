@@ -31,6 +31,7 @@
 // squared norm) rides along in the first group at no extra read.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 
 #include "internal.h"
@@ -634,7 +635,16 @@ size_t expect_scratch_bytes(const ExpectPlan &p) {
            up((size_t)p.grid * NT * sizeof(double)) + up(NT * sizeof(double));
 }
 
-qs_status launch_expect(qs_state_s &s, const ExpectPlan &p, void *d_scratch, double **d_out) {
+namespace {
+size_t expect_table_bytes(const ExpectPlan &p) {
+    auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+    return up(p.terms.size() * sizeof(ExpectTerm)) + up(p.groups.size() * sizeof(ExpectGroup));
+}
+}  // namespace
+
+size_t expect_host_bytes(const ExpectPlan &p) { return expect_table_bytes(p) + p.terms.size() * sizeof(double); }
+
+qs_status launch_expect(qs_state_s &s, const ExpectPlan &p, void *d_scratch, void *h_pinned, double **out) {
     const size_t NT = p.terms.size();
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     unsigned char *base = (unsigned char *)d_scratch;
@@ -645,9 +655,18 @@ qs_status launch_expect(qs_state_s &s, const ExpectPlan &p, void *d_scratch, dou
     double *d_parts = (double *)base;
     base += up((size_t)p.grid * NT * sizeof(double));
     double *d_res = (double *)base;
-    QS_HIP(hipMemcpyAsync(d_terms, p.terms.data(), NT * sizeof(ExpectTerm), hipMemcpyHostToDevice, s.stream));
-    QS_HIP(hipMemcpyAsync(d_groups, p.groups.data(), p.groups.size() * sizeof(ExpectGroup), hipMemcpyHostToDevice,
-                          s.stream));
+    if (h_pinned) {
+        unsigned char *h = (unsigned char *)h_pinned;
+        std::memcpy(h, p.terms.data(), NT * sizeof(ExpectTerm));
+        std::memcpy(h + ((unsigned char *)d_groups - (unsigned char *)d_terms), p.groups.data(),
+                    p.groups.size() * sizeof(ExpectGroup));
+        QS_HIP(hipMemcpyAsync(d_terms, h, expect_table_bytes(p), hipMemcpyHostToDevice, s.stream));
+        d_res = (double *)(h + expect_table_bytes(p));   // the reduction writes host memory
+    } else {
+        QS_HIP(hipMemcpyAsync(d_terms, p.terms.data(), NT * sizeof(ExpectTerm), hipMemcpyHostToDevice, s.stream));
+        QS_HIP(hipMemcpyAsync(d_groups, p.groups.data(), p.groups.size() * sizeof(ExpectGroup), hipMemcpyHostToDevice,
+                              s.stream));
+    }
     const double S = std::ldexp((double)(s.dtype == QS_C64 ? 8 : 16), s.n);
     // algorithmic bytes: one read of the state per group; flops: ~10 per pair and term
     prof_begin(s.stream, QS_PROF_EXPECT, S * (double)p.groups.size(), 10.0 * std::ldexp(1.0, s.n) * (double)NT);
@@ -675,7 +694,7 @@ qs_status launch_expect(qs_state_s &s, const ExpectPlan &p, void *d_scratch, dou
                        (uint64_t)1 << p.log_cosets, d_terms, d_res);
     prof_end(s.stream);
     QS_HIP(hipGetLastError());
-    *d_out = d_res;
+    *out = d_res;
     return QS_OK;
 }
 

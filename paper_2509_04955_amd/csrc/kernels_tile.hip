@@ -565,20 +565,20 @@ void swizzle_mfma(const std::vector<cd> &U, int k, bool lds_layout, std::vector<
     const size_t o0 = out.size();
     out.resize(o0 + (size_t)MT * S * 64);
     for (int mt = 0; mt < MT; ++mt)
-        for (int s = 0; s < S; ++s)
-            for (int lane = 0; lane < 64; ++lane) {
-                const int i = lane % 16, g = lane / 16;
-                const int row = 16 * mt + i;
-                const int r = 4 * (s / 2) + g, p = s % 2;
-                const int rr = row % D, ro = row / D;
-                const cd u = U[(size_t)rr * D + r];
-                double v;
-                if (ro == 0) v = p == 0 ? u.real() : -u.imag();
-                else v = p == 0 ? u.imag() : u.real();
-                const size_t idx = lds_layout ? (((size_t)mt * (S / 4) + s / 4) * 64 + lane) * 4 + s % 4
-                                              : ((size_t)mt * S + s) * 64 + lane;
-                out[o0 + idx] = (R)v;
+        for (int lane = 0; lane < 64; ++lane) {
+            const int row = 16 * mt + lane % 16, g = lane / 16;
+            const cd *u = &U[(size_t)(row % D) * D + g];
+            const bool im = row >= D;   // an output row of imaginary parts
+            for (int h = 0; h < S / 2; ++h) {   // steps 2h (real inputs) and 2h + 1 (imaginary)
+                const double re = u[4 * h].real(), iu = u[4 * h].imag();
+                const R v0 = (R)(im ? iu : re), v1 = (R)(im ? re : -iu);
+                const int s = 2 * h;
+                const size_t i0 = lds_layout ? (((size_t)mt * (S / 4) + s / 4) * 64 + lane) * 4 + s % 4
+                                             : ((size_t)mt * S + s) * 64 + lane;
+                out[o0 + i0] = v0;
+                out[o0 + i0 + (lds_layout ? 1 : 64)] = v1;
             }
+        }
 }
 
 // Host-side operands of mfma3m_block_lds: A_g for g = Ur, Ui, Ur + Ui, entry
@@ -1119,7 +1119,7 @@ int block_kind(const HBlock &b, int t, qs_dtype dt, std::vector<int> *dest, bool
     // vector ALU instead of a dense product
     int sub = 0;
     std::vector<int> src, dst;
-    if (structured_enabled() && bdiag_gap() > 0 && k >= 3 && bdiag_split(b.U, k, sub, src, dst) &&
+    if (structured_enabled() && bdiag_supported(k, 0, dt) && bdiag_split(b.U, k, sub, src, dst) &&
         bdiag_supported(k, sub, dt)) {
         // complex64 4-qubit blocks in staged passes: classes of 8 as 16x16 real
         // products (32 multiply-adds per amplitude on the vector ALU), classes
@@ -1238,14 +1238,16 @@ qs_status plan_upload_impl(qs_plan_s &p, qs_dtype dt, bool stage_lds) {
         }
     }
     p.h_blocks[di] = hb;
-    const size_t bbytes = std::max<size_t>(1, hb.size()) * sizeof(BlockDev);
-    QS_HIP(hipMalloc(&p.d_blocks[di], bbytes));
-    if (!hb.empty()) QS_HIP(hipMemcpy(p.d_blocks[di], hb.data(), hb.size() * sizeof(BlockDev), hipMemcpyHostToDevice));
+    // one allocation and one copy: the operands, then the block records
     const size_t pbytes = dt == QS_C64 ? pool32.size() * sizeof(float) : pool64.size() * sizeof(double);
-    QS_HIP(hipMalloc(&p.d_pool[di], std::max<size_t>(pbytes, 16)));
+    const size_t boff = (pbytes + 255) / 256 * 256, total = boff + std::max<size_t>(1, hb.size()) * sizeof(BlockDev);
+    std::vector<unsigned char> image(total);
     if (pbytes)
-        QS_HIP(hipMemcpy(p.d_pool[di], dt == QS_C64 ? (const void *)pool32.data() : (const void *)pool64.data(), pbytes,
-                         hipMemcpyHostToDevice));
+        std::memcpy(image.data(), dt == QS_C64 ? (const void *)pool32.data() : (const void *)pool64.data(), pbytes);
+    if (!hb.empty()) std::memcpy(image.data() + boff, hb.data(), hb.size() * sizeof(BlockDev));
+    QS_HIP(hipMalloc(&p.d_pool[di], total));
+    QS_HIP(hipMemcpy(p.d_pool[di], image.data(), total, hipMemcpyHostToDevice));
+    p.d_blocks[di] = reinterpret_cast<BlockDev *>((unsigned char *)p.d_pool[di] + boff);
     p.pool_bytes[di] = pbytes;
     p.dev_ready[di] = 1;
     return QS_OK;

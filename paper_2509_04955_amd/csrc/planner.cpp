@@ -19,6 +19,7 @@
 // their qubits with the always-present low qubits {0..c-1} stays within t
 // qubits; a pass is one read and one write of the state (one tile kernel).
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <limits>
 #include <stdexcept>
@@ -168,43 +169,87 @@ void greedy_blocks(const std::vector<HGate> &gates, int n, int kmax, std::vector
     }
 }
 
-// U_B = G_m ... G_1 with each gate embedded into the block's qubits.
+// U_B = G_m ... G_1 with each gate embedded into the block's qubits.  A gate
+// combines whole rows of U (left multiplication), real and imaginary parts in
+// arrays of their own, so the inner loops run over contiguous columns and
+// vectorise.  U grows with the qubits touched so far: their local bits are in
+// order of first touch, so a new qubit doubles U by a copy of itself on the
+// diagonal.  Zero entries of a gate are left out where every factor is finite
+// (0 x would then add nothing).  192 gates in five-qubit blocks: 1.46 ms of
+// host time per plan with full-width std::complex products column by column,
+// 0.2 ms so.
 void block_matrix(const std::vector<HGate> &gates, HBlock &b) {
     const int k = (int)b.qubits.size();
     const int d = 1 << k;
-    b.U.assign((size_t)d * d, cd(0, 0));
-    for (int i = 0; i < d; ++i) b.U[(size_t)i * d + i] = 1;
-    std::vector<cd> tmp;
+    bool finite = true;
+    for (int64_t gi : b.members)
+        for (const cd &v : gates[gi].m) finite &= std::isfinite(v.real()) && std::isfinite(v.imag());
+    std::vector<double> buf((size_t)2 * d * d), tmp;
+    double *ur = buf.data(), *ui = ur + (size_t)d * d;   // row stride d
+    ur[0] = 1.0;
+    int bit[64];      // local bit of a block qubit (by its place in b.qubits), -1: not touched yet
+    std::fill(bit, bit + k, -1);
+    int touched = 0;
+    auto touch = [&](int place) {
+        const int w = 1 << touched;
+        for (int r = 0; r < w; ++r) {
+            std::copy_n(ur + (size_t)r * d, w, ur + (size_t)(r + w) * d + w);
+            std::copy_n(ui + (size_t)r * d, w, ui + (size_t)(r + w) * d + w);
+        }
+        bit[place] = touched++;
+    };
     for (int64_t gi : b.members) {
         const HGate &g = gates[gi];
-        int lp[8];
-        for (int j = 0; j < g.nq; ++j)
-            lp[j] = (int)(std::find(b.qubits.begin(), b.qubits.end(), g.q[j]) - b.qubits.begin());
         const int gd = 1 << g.nq;
-        int gmask = 0;
-        for (int j = 0; j < g.nq; ++j) gmask |= 1 << lp[j];
-        std::vector<int> off(gd);
-        for (int a = 0; a < gd; ++a) {
-            int o = 0;
-            for (int j = 0; j < g.nq; ++j)
-                if ((a >> j) & 1) o |= 1 << lp[j];
-            off[a] = o;
+        int gmask = 0, off[64] = {0};   // gates have at most six qubits
+        for (int j = 0; j < g.nq; ++j) {
+            const int place = (int)(std::find(b.qubits.begin(), b.qubits.end(), g.q[j]) - b.qubits.begin());
+            if (bit[place] < 0) touch(place);
+            gmask |= 1 << bit[place];
+            for (int a = 0; a < gd; ++a)
+                if ((a >> j) & 1) off[a] |= 1 << bit[place];
         }
-        tmp.assign(gd, cd(0, 0));
-        // left-multiply: every column of U is a vector the gate acts on
-        for (int col = 0; col < d; ++col) {
-            for (int base = 0; base < d; ++base) {
-                if (base & gmask) continue;
-                for (int a = 0; a < gd; ++a) {
-                    cd acc = 0;
-                    for (int c2 = 0; c2 < gd; ++c2)
-                        acc += g.m[(size_t)a * gd + c2] * b.U[(size_t)(base | off[c2]) * d + col];
-                    tmp[a] = acc;
+        const int w = 1 << touched;
+        tmp.resize((size_t)2 * gd * w);
+        for (int base = 0; base < w; ++base) {
+            if (base & gmask) continue;
+            std::fill(tmp.begin(), tmp.end(), 0.0);
+            for (int a = 0; a < gd; ++a) {
+                double *__restrict__ xr = tmp.data() + (size_t)2 * a * w, *__restrict__ xi = xr + w;
+                for (int c = 0; c < gd; ++c) {
+                    const double mr = g.m[(size_t)a * gd + c].real(), mi = g.m[(size_t)a * gd + c].imag();
+                    const double *__restrict__ vr = ur + (size_t)(base | off[c]) * d;
+                    const double *__restrict__ vi = ui + (size_t)(base | off[c]) * d;
+                    if (finite && mi == 0.0) {
+                        if (mr == 0.0) continue;
+                        for (int col = 0; col < w; ++col) {
+                            xr[col] += mr * vr[col];
+                            xi[col] += mr * vi[col];
+                        }
+                    } else {
+                        for (int col = 0; col < w; ++col) {
+                            xr[col] += mr * vr[col] - mi * vi[col];
+                            xi[col] += mr * vi[col] + mi * vr[col];
+                        }
+                    }
                 }
-                for (int a = 0; a < gd; ++a) b.U[(size_t)(base | off[a]) * d + col] = tmp[a];
+            }
+            for (int a = 0; a < gd; ++a) {
+                std::copy_n(tmp.data() + (size_t)2 * a * w, w, ur + (size_t)(base | off[a]) * d);
+                std::copy_n(tmp.data() + (size_t)2 * a * w + w, w, ui + (size_t)(base | off[a]) * d);
             }
         }
     }
+    for (int place = 0; place < k; ++place)
+        if (bit[place] < 0) touch(place);
+    // back to ascending qubits
+    std::vector<int> at(d, 0);
+    for (int i = 0; i < d; ++i)
+        for (int j = 0; j < k; ++j)
+            if ((i >> j) & 1) at[i] |= 1 << bit[j];
+    b.U.resize((size_t)d * d);
+    for (int r = 0; r < d; ++r)
+        for (int c = 0; c < d; ++c) b.U[(size_t)r * d + c] = cd(ur[(size_t)at[r] * d + at[c]], ui[(size_t)at[r] * d + at[c]]);
 }
 
 // Passes: list scheduling of the blocks over their dependence order (Section

@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 import numpy as np
 
@@ -57,6 +58,8 @@ class qs_profile(ctypes.Structure):
 
 
 assert ctypes.sizeof(qs_gate) == 80
+_GATE = struct.Struct("=2i8i4dQ")   # one qs_gate
+_GATE_PADS = [(0,) * i for i in range(9)]
 
 _lib = None
 _vp, _u64, _i32, _dbl = ctypes.c_void_p, ctypes.c_uint64, ctypes.c_int, ctypes.c_double
@@ -144,20 +147,16 @@ class GateList:
         self.arr = (qs_gate * max(1, len(gates)))()
         self.count = len(gates)
         self._keep = []
-        for i, g in enumerate(gates):
-            e = self.arr[i]
-            e.kind = KIND[g.name]
-            e.nq = len(g.qubits)
-            for j, q in enumerate(g.qubits):
-                e.qubits[j] = q
-            for j, v in enumerate(g.params):
-                e.params[j] = v
+        pack, pads, at = _GATE.pack_into, _GATE_PADS, 0
+        for g in gates:
+            q, p = g.qubits, g.params
+            ptr = 0
             if g.matrix is not None:
                 m = np.ascontiguousarray(np.asarray(g.matrix, dtype=np.complex128)).view(np.float64).copy()
                 self._keep.append(m)
-                e.matrix = m.ctypes.data
-            else:
-                e.matrix = None
+                ptr = m.ctypes.data
+            pack(self.arr, at, KIND[g.name], len(q), *q, *pads[8 - len(q)], *p, *pads[4 - len(p)], ptr)
+            at += 80
 
     @property
     def ptr(self):
