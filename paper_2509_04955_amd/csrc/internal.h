@@ -79,9 +79,14 @@ struct BlockDev {
     int32_t mat_off;    // offset (reals) of the matrix data in the plan's pool
     int32_t sub;        // BK_BDIAG: log2 of the class width, else 0
     int32_t pos[kMaxK]; // tile positions (ascending) of the block's qubits
-    int32_t pad2[2];
+    // LDS byte offsets (swizzled) that the tile's index bits move an amplitude
+    // by, for the matrix-core paths: of the block's own qubits, and of bit i of
+    // a group number (its i-th free tile position; 0 beyond the last)
+    uint32_t pbit[kMaxK];
+    uint32_t gbit[12];
+    int32_t pad2[4];
 };
-static_assert(sizeof(BlockDev) == 48, "BlockDev layout");
+static_assert(sizeof(BlockDev) == 128, "BlockDev layout");
 
 // Launch arguments of one pass (passed by value).
 struct PassArgs {
@@ -178,6 +183,7 @@ struct qs_plan_s {
     size_t pool_bytes[2] = {0, 0};
     std::vector<qs::BlockDev> h_blocks[2];
     std::vector<uint8_t> pass_wide[2];  // pass needs the wide kernel variant
+    std::vector<uint8_t> pass_lean[2];  // staged pass that a lean variant can run
     // pool range of the pass's block operands staged in LDS (len 0 = none)
     std::vector<int32_t> pass_cl_off[2], pass_cl_len[2];
     ~qs_plan_s();

@@ -121,8 +121,17 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 // compiler three spilled registers, reloaded only in the staged 5- and
 // 6-qubit monomial paths (measured 1.8 % faster per pass than 4 on the
 // 30-qubit UCC circuit); with all 8 the reloads move into the store phase.
-template <typename R, bool WIDE, int NJ, bool CL, int NT = TT>
+//
+// LEAN staged passes (no wide dense or monomial blocks) fit the registers of
+// one or two more waves per SIMD: 2^12-amplitude complex64 tiles run 4
+// workgroups per CU where their operands leave room, 2^12-amplitude complex128
+// tiles 512 threads.  Their blocks are chains of LDS reads, products and
+// writes, and the added waves fill their gaps: brickwork on 28 qubits
+// complex64 1.17 -> 1.13 ms a pass, random circuits on 27 qubits complex128
+// 0.99 -> 0.94 ms.
+template <typename R, bool WIDE, int NJ, bool CL, int NT = TT, bool LEAN = false>
 constexpr int tile_waves() {
+    if (LEAN) return 4;
     // NJ = 0 (tiles below 2^9 complex64 amplitudes) never fills a CU anyway
     if (NT > TT) return 4;
     return WIDE ? 1 : (sizeof(R) == 4 && NJ > 0 && NJ < 16 ? (CL && NJ == 8 ? 3 : 4) : 2);
@@ -146,15 +155,18 @@ constexpr size_t kRedBytes = 128 + 16;   // NT / 64 doubles for up to 1024 threa
 // loads) instead of a reduction launch between the two: scale_in is then the
 // partials.  59 passes on 22 qubits complex64 (2^13 tiles): 45 -> 26 us a pass
 // with its norm; 10 passes on 19 qubits complex128: 45 -> 35 us.
-template <typename R, bool WIDE, int NJ, bool CL, int NT = TT, bool ONE = false>
-__global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT>())) void k_tile_pass(
+template <typename R, bool WIDE, int NJ, bool CL, int NT = TT, bool ONE = false, bool LEAN = false>
+__global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT, LEAN>())) void k_tile_pass(
     typename AmpOf<R>::A *__restrict__ psi, uint64_t ntiles, PassArgs pa, const BlockDev *__restrict__ blocks,
     const R *__restrict__ pool, const double *__restrict__ scale_in, double *__restrict__ partials,
     unsigned long long *__restrict__ tickets, unsigned long long ticket0) {
     using A = typename AmpOf<R>::A;
     constexpr bool F32 = sizeof(R) == 4;
     constexpr uint32_t APV = F32 ? 2 : 1;  // amplitudes per 16-byte vector
-    constexpr int PFMAX = NT > TT && CL ? 6 : tile_waves<R, WIDE, NJ, CL, NT>() <= 3 ? (sizeof(R) == 8 ? 8 : 16) : kPrefetch;
+    constexpr int PFMAX = LEAN ? (F32 ? 6 : 8)
+                          : NT > TT && CL ? 6
+                          : tile_waves<R, WIDE, NJ, CL, NT>() <= 3 ? (sizeof(R) == 8 ? 8 : 16)
+                                                                   : kPrefetch;
     constexpr int PF = NJ > 0 ? (NJ < PFMAX ? NJ : PFMAX) : kPrefetch;
     constexpr int EX = NJ > PF ? NJ - PF : 0;   // compile-time tiles: vectors loaded after the blocks
     static_assert(NT / 64 * sizeof(double) + 2 * sizeof(uint64_t) <= kRedBytes, "norm and ticket slots");
@@ -256,7 +268,7 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT>())) void k_til
         __syncthreads();
         for (int b = 0; b < pa.nblocks; ++b) {
             if (blocks[pa.block0 + b].kind == BK_SKIP) continue;   // folded into a group (uniform)
-            apply_block<R, WIDE, CL, NT>(tl, T, blocks + pa.block0 + b, pool, base, cst, pa.cl_off);
+            apply_block<R, WIDE, CL, NT, true, LEAN>(tl, T, blocks + pa.block0 + b, pool, base, cst, pa.cl_off);
             __syncthreads();
         }
         double nacc = 0.0;
@@ -346,7 +358,7 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT>())) void k_til
         // ---- blocks ----
         for (int b = 0; b < pa.nblocks; ++b) {
             if (blocks[pa.block0 + b].kind == BK_SKIP) continue;   // folded into a group (uniform)
-            apply_block<R, WIDE, CL, NT>(tl, T, blocks + pa.block0 + b, pool, base, cst, pa.cl_off);
+            apply_block<R, WIDE, CL, NT, true, LEAN>(tl, T, blocks + pa.block0 + b, pool, base, cst, pa.cl_off);
             __syncthreads();
         }
         V ex[EX > 0 ? EX : 1];
@@ -470,12 +482,16 @@ using TileKernel = void (*)(typename AmpOf<R>::A *, uint64_t, PassArgs, const Bl
 // (cl), a workgroup per tile (ONE) and, for the narrow variant and wide ONE
 // passes of complex128, the compile-time vector count.
 template <typename R, bool ONE>
-TileKernel<R> pick_tile_kernel(bool wide, int t, bool cl, int &threads, bool &static_tile) {
+TileKernel<R> pick_tile_kernel(bool wide, int t, bool cl, bool lean, int &threads, bool &static_tile) {
     constexpr int APV = sizeof(R) == 4 ? 2 : 1;
     const int vpt = (1 << t) / (TT * APV);   // 16-byte vectors per thread
     threads = TT;
     static_tile = false;
     if (wide) return k_tile_pass<R, true, 0, false, TT, ONE>;
+    if (cl && lean && t == 12) {
+        threads = sizeof(R) == 4 ? 256 : 512;
+        return k_tile_pass<R, false, 8, true, sizeof(R) == 4 ? 256 : 512, ONE, true>;
+    }
     if constexpr (sizeof(R) == 4) {
         // unstaged 2^13 / 2^14 tiles: more threads per workgroup, 8 vectors each
         if (!cl && big_tiles_enabled()) {
@@ -554,9 +570,10 @@ bool mfma_enabled() {
     return v == 1;
 }
 
-// Host-side A-operand swizzle of a complex64 block: entry (R, kk) of the
+// Host-side A-operand swizzle of a block: entry (R, kk) of the
 // real embedding [[Ur, -Ui], [Ui, Ur]] for M-tile mt, step s and lane l is row
-// R = 16 mt + l % 16 and input (row 4 (s / 2) + l / 16, part s % 2).
+// R = 16 mt + l % 16 (in the LDS layout ordered by amplitude, see lds_row_amp)
+// and input (row 4 (s / 2) + l / 16, part s % 2).
 // Layout [mt][s][lane] for mfma_block, [mt][s / 4][lane][s % 4] for
 // mfma_block_lds (16-byte LDS reads).
 template <typename R>
@@ -566,9 +583,9 @@ void swizzle_mfma(const std::vector<cd> &U, int k, bool lds_layout, std::vector<
     out.resize(o0 + (size_t)MT * S * 64);
     for (int mt = 0; mt < MT; ++mt)
         for (int lane = 0; lane < 64; ++lane) {
-            const int row = 16 * mt + lane % 16, g = lane / 16;
-            const cd *u = &U[(size_t)(row % D) * D + g];
-            const bool im = row >= D;   // an output row of imaginary parts
+            const int i = lane % 16, row = 16 * mt + i, g = lane / 16;
+            const cd *u = &U[(size_t)(lds_layout ? lds_row_amp<R>(mt, i) : row % D) * D + g];
+            const bool im = lds_layout ? lds_row_part<R>(i) : row >= D;   // an output row of imaginary parts
             for (int h = 0; h < S / 2; ++h) {   // steps 2h (real inputs) and 2h + 1 (imaginary)
                 const double re = u[4 * h].real(), iu = u[4 * h].imag();
                 const R v0 = (R)(im ? iu : re), v1 = (R)(im ? re : -iu);
@@ -1167,6 +1184,30 @@ bool pass_staged(const std::vector<HBlock> &blocks, const HPass &ps, qs_dtype dt
 
 namespace {
 qs_status plan_upload_impl(qs_plan_s &p, qs_dtype dt, bool stage_lds);
+
+// QS_TILE_LEAN=0: staged passes keep the general variants
+bool lean_enabled() {
+    static int v = -1;
+    if (v < 0) {
+        const char *e = getenv("QS_TILE_LEAN");
+        v = e ? atoi(e) != 0 : 1;
+    }
+    return v == 1;
+}
+
+// Whether a staged pass (its operands take `bytes`) can run a lean variant:
+// 2^12-amplitude tiles, blocks within the variant's widths, and for complex64
+// operands that leave room for the fourth workgroup of a CU.
+bool lean_pass(const std::vector<HBlock> &blocks, const HPass &ps, qs_dtype dt, size_t bytes) {
+    if (!lean_enabled() || ps.t != 12) return false;
+    if (dt == QS_C64 && (8u << 12) + kRedBytes + bytes > 40 * 1024) return false;
+    for (int64_t b = ps.block0; b < ps.block0 + ps.nblocks; ++b) {
+        const int k = (int)blocks[b].qubits.size();
+        const int kind = block_kind(blocks[b], ps.t, dt, nullptr, true);
+        if (dt == QS_C64 ? (kind == BK_MFMA || kind == BK_MONO) && k > 4 : kind == BK_PAULI || k > 3) return false;
+    }
+    return true;
+}
 }  // namespace
 
 // Host invariants of the records (a rotation's X part inside its tile, a
@@ -1191,6 +1232,7 @@ qs_status plan_upload_impl(qs_plan_s &p, qs_dtype dt, bool stage_lds) {
     std::vector<float> pool32;
     std::vector<double> pool64;
     p.pass_wide[di].assign(p.passes.size(), 0);
+    p.pass_lean[di].assign(p.passes.size(), 0);
     p.pass_cl_off[di].assign(p.passes.size(), 0);
     p.pass_cl_len[di].assign(p.passes.size(), 0);
     for (size_t pi = 0; pi < p.passes.size(); ++pi) {
@@ -1227,6 +1269,10 @@ qs_status plan_upload_impl(qs_plan_s &p, qs_dtype dt, bool stage_lds) {
                      "block width %d unsupported for this dtype", d.k);
             for (int j = 0; j < d.k; ++j)
                 d.pos[j] = (int)(std::find(ps.tile.begin(), ps.tile.end(), blk.qubits[j]) - ps.tile.begin());
+            const uint32_t amp = dt == QS_C64 ? 8 : 16;
+            for (int j = 0; j < d.k; ++j) d.pbit[j] = sw(1u << d.pos[j]) * amp;
+            for (int q = 0, i = 0; q < ps.t && i < 12; ++q)
+                if (std::find(d.pos, d.pos + d.k, q) == d.pos + d.k) d.gbit[i++] = sw(1u << q) * amp;
             if (dt == QS_C64) push_block<float>(blk, d, ps.t, dt, lds, pool32, wide);
             else push_block<double>(blk, d, ps.t, dt, lds, pool64, wide);
         }
@@ -1235,6 +1281,7 @@ qs_status plan_upload_impl(qs_plan_s &p, qs_dtype dt, bool stage_lds) {
             const size_t pool1 = dt == QS_C64 ? pool32.size() : pool64.size();
             p.pass_cl_off[di][pi] = (int32_t)pool0;
             p.pass_cl_len[di][pi] = (int32_t)(pool1 - pool0);
+            p.pass_lean[di][pi] = lean_pass(p.blocks, ps, dt, (pool1 - pool0) * (dt == QS_C64 ? 4 : 8));
         }
     }
     p.h_blocks[di] = hb;
@@ -1283,6 +1330,7 @@ struct PassLaunch {
 qs_status pass_launch(const qs_state_s &s, const qs_plan_s &p, const HPass &ps, int64_t pass_index, PassLaunch &L) {
     const int di = s.dtype == QS_C64 ? 0 : 1;
     const bool wide = p.pass_wide[di][pass_index] != 0, cl = p.pass_cl_len[di][pass_index] > 0;
+    const bool lean = p.pass_lean[di][pass_index] != 0;
     const size_t amp = s.dtype == QS_C64 ? 8 : 16;
     L.ntiles = 1ull << (s.n - ps.t);
     for (const bool one : {true, false}) {
@@ -1290,11 +1338,11 @@ qs_status pass_launch(const qs_state_s &s, const qs_plan_s &p, const HPass &ps, 
         L.k32 = nullptr;
         L.k64 = nullptr;
         if (s.dtype == QS_C64)
-            L.k32 = one ? pick_tile_kernel<float, true>(wide, ps.t, cl, L.threads, static_tile)
-                        : pick_tile_kernel<float, false>(wide, ps.t, cl, L.threads, static_tile);
+            L.k32 = one ? pick_tile_kernel<float, true>(wide, ps.t, cl, lean, L.threads, static_tile)
+                        : pick_tile_kernel<float, false>(wide, ps.t, cl, lean, L.threads, static_tile);
         else
-            L.k64 = one ? pick_tile_kernel<double, true>(wide, ps.t, cl, L.threads, static_tile)
-                        : pick_tile_kernel<double, false>(wide, ps.t, cl, L.threads, static_tile);
+            L.k64 = one ? pick_tile_kernel<double, true>(wide, ps.t, cl, lean, L.threads, static_tile)
+                        : pick_tile_kernel<double, false>(wide, ps.t, cl, lean, L.threads, static_tile);
         // dynamic LDS: none for the static-tile variants, else tile + norm slots + staged operands
         L.lds = static_tile ? 0
                             : (amp << ps.t) + kRedBytes +

@@ -150,9 +150,41 @@ __device__ __forceinline__ uint32_t lane_part(const TL &tl, uint32_t jc, const i
     return tl.grp(sw(c) * bytes);
 }
 
+// Staged matrix-core blocks take the same offsets from the block's record: an
+// amplitude's LDS offset is linear over the
+// bits of its group number and of its place in the group, and the block's
+// record holds the offset of every one of those bits: an address is an XOR of
+// record entries, picked per lane (the column, the lane's rows) once per block
+// and on the scalar unit per chunk.  Inserting the zero bits and swizzling at
+// run time instead took a third of the block's issue slots.  (The pool form of
+// mfma_block keeps the run-time form: with the record's its unstaged kernels
+// allocate registers so that the store phase waits for the prefetch, and
+// rotation passes on 27 qubits went from 0.403 to 0.421 ms.)
+template <int B>
+__device__ __forceinline__ uint32_t pick_uniform(uint32_t v, const uint32_t *__restrict__ bits) {
+    uint32_t r = 0;
+#pragma unroll
+    for (int i = 0; i < B; ++i) r ^= (v >> i) & 1u ? bits[i] : 0u;
+    return r;
+}
+template <int B>
+__device__ __forceinline__ uint32_t pick_lane(uint32_t v, const uint32_t *__restrict__ bits) {
+    uint32_t r = 0;
+#pragma unroll
+    for (int i = 0; i < B; ++i) r ^= bits[i] & (0u - ((v >> i) & 1u));
+    return r;
+}
+constexpr int log2i(int v) { return v <= 1 ? 0 : 1 + log2i(v / 2); }
+
 // A 32-bit pattern stored in an operand pool entry (bit-cast, not converted).
 __device__ __forceinline__ uint32_t pool_bits(float v) { return __float_as_uint(v); }
 __device__ __forceinline__ uint32_t pool_bits(double v) { return (uint32_t)__double_as_longlong(v); }
+
+// Between a matrix-core block's LDS reads and its products: nothing is moved
+// across.  Left to itself the scheduler, short of registers beside the tile
+// prefetch, put each read right before the product that needs it, and a wave
+// waited an LDS latency per product.
+__device__ __forceinline__ void reads_first() { __builtin_amdgcn_sched_barrier(0); }
 
 // ---- vector-ALU block: one group of 2^K amplitudes per lane -------------
 // Two groups per iteration when K <= 3 so each lane has independent LDS
@@ -182,7 +214,7 @@ __device__ __forceinline__ void dense_group(TL tl, uint32_t h, const uint32_t *o
     }
 }
 
-template <int K, typename R, int NT = TT, typename TL>
+template <int K, typename R, int NT = TT, bool PAIR = (K <= 3), typename TL>
 __device__ __forceinline__ void valu_block(TL tl, int T, const BlockDev *bd, const R *__restrict__ U) {
     using A = typename AmpOf<R>::A;
     constexpr int D = 1 << K;
@@ -205,7 +237,7 @@ __device__ __forceinline__ void valu_block(TL tl, int T, const BlockDev *bd, con
         for (int j = 0; j < K; ++j) b = ins0_32(b, pos[j]);
         return tl.grp(sw(b) * (uint32_t)sizeof(A));
     };
-    if constexpr (K <= 3) {
+    if constexpr (PAIR) {
         if (G >= 2 * NT) {
             // G is a power of two >= 512: every lane has exactly G / 512 pairs of groups
             for (uint32_t g = threadIdx.x; g < G; g += 2 * NT) {
@@ -656,16 +688,32 @@ __device__ __forceinline__ void mfma_block(TL tl, int T, const BlockDev *bd, con
     }
 }
 
-// ---- MFMA block with the A operand in LDS (complex64, K = 3, 4, 5) --------
+// ---- MFMA block with the A operand in LDS (K = 3, 5) -------------------------
 // The same real GEMM as mfma_block, organised for a pass whose block operands
 // were staged in LDS: each wave owns whole 16-column chunks and runs every
-// M-tile over them, re-reading A from LDS (16-byte reads, layout
-// [M-tile][step/4][lane][4]).  A chunk's inputs are all in registers before
-// any of its outputs is written and no other wave touches the chunk, so the
-// block needs no barrier of its own.  Output row R = 16 m + 4 (lane/16) + q is
-// amplitude R mod 2^K, real part when R < 2^K (K = 3 has one M-tile holding
-// both parts); for FP64 the row of item q is 16 m + lane/16 + 4q.  CPI chunks are in flight per wave (CPI * MT accumulator
-// chains).
+// M-tile over them (layout of A: [M-tile][step/4][lane][4]).  A chunk's inputs
+// are all in registers before any of its outputs is written and no other wave
+// touches the chunk, so the block needs no barrier of its own.  Staged passes
+// have tiles of 2^11 and more (lds_operand_budget), whose chunks come out even
+// over the waves and the chunks in flight.  The rows of A are ordered so that a lane's four outputs are two whole amplitudes
+// (lds_row), each written in one access: as [Re; Im] rows they were four
+// scalar writes that met half of the banks.  K = 3 keeps A in registers and
+// has four chunks (four accumulator chains) in flight per wave, so that one
+// iteration's LDS reads and address work cover the others' products; K = 5
+// re-reads A per chunk.  Brickwork on 28 qubits, 2^12 tiles, five 3-qubit
+// blocks a pass, complex64: 1.30 -> 1.17 ms a pass,
+// with the addresses from the record; complex128 random circuits 1.00 -> 0.99.
+//
+// Amplitude and part of row i of M-tile m (the output items q of lane group g
+// are rows Mfma::row(g, q)).
+template <typename R>
+__host__ __device__ constexpr int lds_row_amp(int m, int i) {
+    return sizeof(R) == 4 ? 8 * m + i / 2 : 8 * m + i % 4 + 4 * (i / 8);
+}
+template <typename R>
+__host__ __device__ constexpr int lds_row_part(int i) {
+    return sizeof(R) == 4 ? i % 2 : (i / 4) % 2;
+}
 template <int K, typename R, int NT = TT, typename TL>
 __device__ __forceinline__ void mfma_block_lds(TL tl, int T, const BlockDev *bd, const R *As) {
     using A = typename AmpOf<R>::A;
@@ -674,46 +722,47 @@ __device__ __forceinline__ void mfma_block_lds(TL tl, int T, const BlockDev *bd,
     constexpr int MT = 2 * D / 16;
     constexpr int S = 2 * D / 4;
     constexpr int NB = D / 4;
-    constexpr int CPI = K >= 5 ? 1 : 2;
+    constexpr int CPI = K >= 5 ? 1 : sizeof(R) == 4 ? 4 : 2;
+    constexpr bool HOIST = K == 3;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int gq = lane >> 4, jc = lane & 15;
-    int pos[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) pos[j] = bd->pos[j];
-    auto deposit = [&](int r) {
-        uint32_t o = 0;
-#pragma unroll
-        for (int j = 0; j < K; ++j)
-            if ((r >> j) & 1) o |= 1u << pos[j];
-        return o;
-    };
+    const uint32_t *pb = bd->pbit, *gb = bd->gbit;
+    // input row 4 m + gq
+    const uint32_t in_l = pick_lane<2>((uint32_t)gq, pb);
     uint32_t offB[NB];
 #pragma unroll
-    for (int m = 0; m < NB; ++m) offB[m] = sw(deposit(4 * m + gq)) * (uint32_t)sizeof(A);
-    // byte offset of output (m, q) from the chunk column's amplitude:
-    // sw(row offset) amplitudes, plus one real for the imaginary rows
-    uint32_t oc[MT][4];
+    for (int m = 0; m < NB; ++m) offB[m] = in_l ^ pick_uniform<K - 2>((uint32_t)m, pb + 2);
+    // this lane's two output amplitudes (items 2h and 2h + 1): 8 m + 2 gq + h,
+    // for FP64 8 m + gq + 4 h (lds_row_amp)
+    constexpr int GB = sizeof(R) == 4 ? 1 : 0, HB = sizeof(R) == 4 ? 0 : 2;
+    const uint32_t out_l = pick_lane<2>((uint32_t)gq, pb + GB);
+    uint32_t oc[MT][2];
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int row = 16 * m + Mfma<R>::row(gq, q);
-            oc[m][q] = ((2u * sw(deposit(row % D))) | (uint32_t)(row / D)) * (uint32_t)sizeof(R);
-        }
+        for (int h = 0; h < 2; ++h)
+            oc[m][h] = out_l ^ pick_uniform<1>((uint32_t)h, pb + HB) ^ pick_uniform<K - 3>((uint32_t)m, pb + 3);
     const V4 *A4 = reinterpret_cast<const V4 *>(As);
-    const uint32_t nchunks = (1u << (T - K)) / 16;
-    const uint32_t hj = lane_part<K>(tl, (uint32_t)jc, pos, (uint32_t)sizeof(A));
-    for (uint32_t ch0 = (uint32_t)wave * CPI; ch0 < nchunks; ch0 += (NT / 64) * CPI) {
+    V4 ah[HOIST ? MT * (S / 4) : 1];
+    if constexpr (HOIST) {
+#pragma unroll
+        for (int i = 0; i < MT * (S / 4); ++i) ah[i] = A4[i * 64 + lane];
+    }
+    constexpr int LC = log2i(CPI), LW = log2i(NT / 64);
+    const uint32_t rounds = (1u << (T - K)) / (16 * CPI * (NT / 64));
+    const uint32_t hj = tl.grp(pick_lane<4>((uint32_t)jc, gb)) ^ pick_uniform<LW>((uint32_t)wave, gb + 4 + LC);
+    for (uint32_t r = 0; r < rounds; ++r) {
+        const uint32_t hr = hj ^ pick_uniform<3>(r, gb + 4 + LC + LW);
         uint32_t cb[CPI];
         A bv[CPI][NB];
 #pragma unroll
         for (int h = 0; h < CPI; ++h) {
-            const uint32_t ch = ch0 + h < nchunks ? ch0 + h : ch0;   // a short last round re-reads a valid chunk
-            cb[h] = hj ^ chunk_part<K>(ch, pos, (uint32_t)sizeof(A));
+            cb[h] = hr ^ pick_uniform<LC>((uint32_t)h, gb + 4);
 #pragma unroll
             for (int m = 0; m < NB; ++m) bv[h][m] = *tl.template at<A>(cb[h], offB[m]);
         }
+        reads_first();
         V4 acc[CPI][MT];
 #pragma unroll
         for (int h = 0; h < CPI; ++h)
@@ -723,7 +772,7 @@ __device__ __forceinline__ void mfma_block_lds(TL tl, int T, const BlockDev *bd,
         for (int s4 = 0; s4 < S / 4; ++s4) {
             V4 a[MT];
 #pragma unroll
-            for (int m = 0; m < MT; ++m) a[m] = A4[(m * (S / 4) + s4) * 64 + lane];
+            for (int m = 0; m < MT; ++m) a[m] = HOIST ? ah[m * (S / 4) + s4] : A4[(m * (S / 4) + s4) * 64 + lane];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int s = 4 * s4 + u;
@@ -735,14 +784,16 @@ __device__ __forceinline__ void mfma_block_lds(TL tl, int T, const BlockDev *bd,
             }
         }
 #pragma unroll
-        for (int h = 0; h < CPI; ++h) {
-            if (ch0 + h < nchunks) {
+        for (int h = 0; h < CPI; ++h)
 #pragma unroll
-                for (int m = 0; m < MT; ++m)
+            for (int m = 0; m < MT; ++m)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) *tl.template at<R>(cb[h], oc[m][q]) = acc[h][m][q];
-            }
-        }
+                for (int i = 0; i < 2; ++i) {
+                    A y;
+                    y.x = acc[h][m][2 * i];
+                    y.y = acc[h][m][2 * i + 1];
+                    *tl.template at<A>(cb[h], oc[m][i]) = y;
+                }
     }
 }
 
@@ -772,24 +823,20 @@ __device__ __forceinline__ void mfma3m_block_lds(TL tl, int T, const BlockDev *b
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int gq = lane >> 4, jc = lane & 15;
-    int pos[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) pos[j] = bd->pos[j];
-    auto deposit = [&](int r) {
-        uint32_t o = 0;
-#pragma unroll
-        for (int j = 0; j < K; ++j)
-            if ((r >> j) & 1) o |= 1u << pos[j];
-        return o;
-    };
+    const uint32_t *pb = bd->pbit, *gb = bd->gbit;
+    const uint32_t in_l = pick_lane<2>((uint32_t)gq, pb);   // input row 4 s + gq
     uint32_t offB[S];
 #pragma unroll
-    for (int s = 0; s < S; ++s) offB[s] = sw(deposit(4 * s + gq)) * (uint32_t)sizeof(A);
+    for (int s = 0; s < S; ++s) offB[s] = in_l ^ pick_uniform<K - 2>((uint32_t)s, pb + 2);
+    // output row 16 m + Mfma::row(gq, q): the lane's bits sit at row(1, 0), q's at row(0, 1)
+    constexpr int GB = log2i(Mfma<R>::row(1, 0)), QB = log2i(Mfma<R>::row(0, 1));
+    const uint32_t out_l = pick_lane<2>((uint32_t)gq, pb + GB);
     uint32_t oc[MT][4];
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) oc[m][q] = sw(deposit(16 * m + Mfma<R>::row(gq, q))) * (uint32_t)sizeof(A);
+        for (int q = 0; q < 4; ++q)
+            oc[m][q] = out_l ^ pick_uniform<2>((uint32_t)q, pb + QB) ^ pick_uniform<K - 4>((uint32_t)m, pb + 4);
     const V4 *A4 = reinterpret_cast<const V4 *>(As);
     auto aidx = [&](int g, int m, int s4) { return ((g * MT + m) * S4 + s4) * 64 + lane; };
     V4 ah[HOIST ? 3 * MT * S4 : 1];
@@ -801,18 +848,20 @@ __device__ __forceinline__ void mfma3m_block_lds(TL tl, int T, const BlockDev *b
 #pragma unroll
                 for (int s4 = 0; s4 < S4; ++s4) ah[(g * MT + m) * S4 + s4] = A4[aidx(g, m, s4)];
     }
-    const uint32_t nchunks = (1u << (T - K)) / 16;
-    const uint32_t hj = lane_part<K>(tl, (uint32_t)jc, pos, (uint32_t)sizeof(A));
-    for (uint32_t ch0 = (uint32_t)wave * CPI; ch0 < nchunks; ch0 += (NT / 64) * CPI) {
+    constexpr int LC = log2i(CPI), LW = log2i(NT / 64);
+    const uint32_t rounds = (1u << (T - K)) / (16 * CPI * (NT / 64));
+    const uint32_t hj = tl.grp(pick_lane<4>((uint32_t)jc, gb)) ^ pick_uniform<LW>((uint32_t)wave, gb + 4 + LC);
+    for (uint32_t r = 0; r < rounds; ++r) {
+        const uint32_t hr = hj ^ pick_uniform<3>(r, gb + 4 + LC + LW);
         uint32_t cb[CPI];
         A bv[CPI][S];
 #pragma unroll
         for (int h = 0; h < CPI; ++h) {
-            const uint32_t ch = ch0 + h < nchunks ? ch0 + h : ch0;   // a short last round re-reads a valid chunk
-            cb[h] = hj ^ chunk_part<K>(ch, pos, (uint32_t)sizeof(A));
+            cb[h] = hr ^ pick_uniform<LC>((uint32_t)h, gb + 4);
 #pragma unroll
             for (int s = 0; s < S; ++s) bv[h][s] = *tl.template at<A>(cb[h], offB[s]);
         }
+        reads_first();
         V4 acc[CPI][3][MT];
 #pragma unroll
         for (int h = 0; h < CPI; ++h)
@@ -842,20 +891,17 @@ __device__ __forceinline__ void mfma3m_block_lds(TL tl, int T, const BlockDev *b
             }
         }
 #pragma unroll
-        for (int h = 0; h < CPI; ++h) {
-            if (ch0 + h < nchunks) {
+        for (int h = 0; h < CPI; ++h)
 #pragma unroll
-                for (int m = 0; m < MT; ++m)
+            for (int m = 0; m < MT; ++m)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const R t1 = acc[h][0][m][q], t2 = acc[h][1][m][q], t3 = acc[h][2][m][q];
-                        A y;
-                        y.x = t1 - t2;
-                        y.y = t3 - t1 - t2;
-                        *tl.template at<A>(cb[h], oc[m][q]) = y;
-                    }
-            }
-        }
+                for (int q = 0; q < 4; ++q) {
+                    const R t1 = acc[h][0][m][q], t2 = acc[h][1][m][q], t3 = acc[h][2][m][q];
+                    A y;
+                    y.x = t1 - t2;
+                    y.y = t3 - t1 - t2;
+                    *tl.template at<A>(cb[h], oc[m][q]) = y;
+                }
     }
 }
 
@@ -882,9 +928,7 @@ __device__ __forceinline__ void bdiag_mfma_block(TL tl, int T, const BlockDev *b
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, jc = lane & 15;
-    int pos[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) pos[j] = bd->pos[j];
+    const uint32_t *gb = bd->gbit;
     // per pack: this lane's A values, its 4 column offsets (with the part's
     // 4-byte shift), its 2 row offsets
     floatx4 a[NPK];
@@ -900,40 +944,38 @@ __device__ __forceinline__ void bdiag_mfma_block(TL tl, int T, const BlockDev *b
         oo[p][0] = ob[0];
         oo[p][1] = ob[1];
     }
-    const uint32_t nchunks = (1u << (T - K)) / 16;
-    const uint32_t hj = lane_part<K>(tl, (uint32_t)jc, pos, (uint32_t)sizeof(float2));
-    for (uint32_t ch0 = (uint32_t)wave * CPI; ch0 < nchunks; ch0 += (NT / 64) * CPI) {
+    constexpr int LC = log2i(CPI), LW = log2i(NT / 64);
+    const uint32_t rounds = (1u << (T - K)) / (16 * CPI * (NT / 64));
+    const uint32_t hj = tl.grp(pick_lane<4>((uint32_t)jc, gb)) ^ pick_uniform<LW>((uint32_t)wave, gb + 4 + LC);
+    for (uint32_t r = 0; r < rounds; ++r) {
+        const uint32_t hr = hj ^ pick_uniform<3>(r, gb + 4 + LC + LW);
         uint32_t sb[CPI];
         float x[CPI][NPK][4];
 #pragma unroll
         for (int h = 0; h < CPI; ++h) {
-            const uint32_t ch = ch0 + h < nchunks ? ch0 + h : ch0;   // a short last round re-reads a valid chunk
-            sb[h] = hj ^ chunk_part<K>(ch, pos, (uint32_t)sizeof(float2));
+            sb[h] = hr ^ pick_uniform<LC>((uint32_t)h, gb + 4);
 #pragma unroll
             for (int p = 0; p < NPK; ++p)
 #pragma unroll
                 for (int s = 0; s < 4; ++s) x[h][p][s] = *tl.template at<const float>(sb[h], io[p][s]);
         }
+        reads_first();
         floatx4 acc[CPI][NPK];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int h = 0; h < CPI; ++h)
+#pragma unroll
+                for (int p = 0; p < NPK; ++p)
+                    acc[h][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        a[p][s], x[h][p][s], s ? acc[h][p] : floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
 #pragma unroll
         for (int h = 0; h < CPI; ++h)
 #pragma unroll
             for (int p = 0; p < NPK; ++p) {
-                acc[h][p] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-                    acc[h][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[p][s], x[h][p][s], acc[h][p], 0, 0, 0);
+                *tl.template at<float2>(sb[h], oo[p][0]) = make_float2(acc[h][p][0], acc[h][p][1]);
+                *tl.template at<float2>(sb[h], oo[p][1]) = make_float2(acc[h][p][2], acc[h][p][3]);
             }
-#pragma unroll
-        for (int h = 0; h < CPI; ++h) {
-            if (ch0 + h < nchunks) {
-#pragma unroll
-                for (int p = 0; p < NPK; ++p) {
-                    *tl.template at<float2>(sb[h], oo[p][0]) = make_float2(acc[h][p][0], acc[h][p][1]);
-                    *tl.template at<float2>(sb[h], oo[p][1]) = make_float2(acc[h][p][2], acc[h][p][3]);
-                }
-            }
-        }
     }
 }
 
@@ -1025,7 +1067,10 @@ __device__ __forceinline__ void class_mfma_block(TL tl, int T, const BlockDev *b
 // narrow monomial blocks keep their wave-uniform scalar loads from the pool.
 // PG: rotation groups and coefficient forms compiled in (the single-state pass
 // kernel); the batch kernel leaves them out to keep its register budget.
-template <typename R, bool WIDE, bool CL = false, int NT = TT, bool PG = true, typename TL>
+// LEAN (staged passes): complex64 without dense or monomial blocks wider than 4
+// qubits, complex128 without rotations and without any block wider than 3:
+// their paths need registers that cost a wave.
+template <typename R, bool WIDE, bool CL = false, int NT = TT, bool PG = true, bool LEAN = false, typename TL>
 __device__ __forceinline__ void apply_block(TL tile, int T, const BlockDev *bd,
                                             const R *__restrict__ pool, uint64_t gbase, const R *cst = nullptr,
                                             int cl_off = 0) {
@@ -1033,6 +1078,23 @@ __device__ __forceinline__ void apply_block(TL tile, int T, const BlockDev *bd,
     const int kind = bd->kind;
     const R *U = pool + bd->mat_off;
     constexpr bool F32 = sizeof(R) == 4;
+    if constexpr (LEAN && !F32) {
+        if (kind == BK_MFMA) {
+            mfma_block_lds<3, R, NT>(tile, T, bd, cst + (bd->mat_off - cl_off));
+        } else if (kind == BK_BDIAG) {
+            if (bd->sub == 1) bdiag_block<3, 1, R, NT>(tile, T, bd, U);
+            else bdiag_block<3, 2, R, NT>(tile, T, bd, U);
+        } else if (kind == BK_MONO) {
+            if (k == 1) mono_block<1, R, NT>(tile, T, bd, U);
+            else if (k == 2) mono_block<2, R, NT>(tile, T, bd, U);
+            else mono_block<3, R, NT>(tile, T, bd, U);
+        } else {
+            if (k == 1) valu_block<1, R, NT>(tile, T, bd, U);
+            else if (k == 2) valu_block<2, R, NT>(tile, T, bd, U);
+            else valu_block<3, R, NT, false>(tile, T, bd, U);   // one group per lane at these sizes
+        }
+        return;
+    }
     if (kind == BK_PAULI) {
         if constexpr (PG) pauli_block<R, NT>(tile, T, U, gbase, bd->sub);
         else pauli_block_m<R, NT, 0>(tile, T, U, gbase);
@@ -1058,7 +1120,7 @@ __device__ __forceinline__ void apply_block(TL tile, int T, const BlockDev *bd,
         if constexpr (CL) {
             const R *As = cst + (bd->mat_off - cl_off);
             if (k == 3) mfma_block_lds<3, R, NT>(tile, T, bd, As);
-            else if (k == 4) mfma3m_block_lds<4, R, NT>(tile, T, bd, As);
+            else if (LEAN || k == 4) mfma3m_block_lds<4, R, NT>(tile, T, bd, As);
             else if constexpr (NT > TT) mfma_block_lds<5, R, NT>(tile, T, bd, As);
             else mfma3m_block_lds<5, R, NT>(tile, T, bd, As);
             return;
@@ -1101,6 +1163,10 @@ __device__ __forceinline__ void apply_block(TL tile, int T, const BlockDev *bd,
         }
         if constexpr (CL) {
             const R *E = cst + (bd->mat_off - cl_off);
+            if constexpr (LEAN) {
+                mono_block<4, R, NT>(tile, T, bd, E);
+                return;
+            }
             switch (k) {
             case 4: mono_block<4, R, NT>(tile, T, bd, E); return;
             case 5: mono_block<5, R, NT>(tile, T, bd, E); return;

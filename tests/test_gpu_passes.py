@@ -28,6 +28,9 @@ def Q():
     (0, 20, 3, 9), (0, 21, 3, 9), (0, 22, 4, 13), (0, 23, 4, 13),
     (1, 6, 3, 12), (1, 13, 5, 12), (1, 13, 3, 12), (1, 14, 5, 11), (1, 16, 2, 7), (1, 20, 3, 8), (1, 21, 3, 12),
     (1, 22, 3, 12),
+    # staged passes: lean (blocks of up to 3 or 4 qubits at 2^12) and general ones, resident and not
+    (0, 18, 3, 12), (0, 18, 4, 12), (0, 18, 5, 12), (0, 23, 3, 12), (0, 16, 5, 11), (0, 21, 5, 13),
+    (1, 18, 3, 12), (1, 16, 4, 11), (1, 16, 5, 12),
 ])
 def test_pass_chain(Q, oracle, dtype, n, k, t, renorm):
     """A plan applied twice to a random state of norm 3 (renorm: the chain of
