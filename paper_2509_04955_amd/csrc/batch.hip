@@ -399,12 +399,14 @@ qs_status qs_batch_create(int n_states, const int *n_qubits, const qs_gate *cons
         uint64_t tiles = 0;
         for (int i = 0; i < n_states; ++i)
             if (pi < b->plans[i]->passes.size()) tiles += 1ull << (b->n[i] - b->plans[i]->passes[pi].t);
-        // tiles per item: 1 until the level has six items per CU (two rounds of
-        // the three workgroups a CU holds), then more, so that an item's next
-        // tile is in flight during its current one; 16 at most, but enough
-        // that a pass leaves at most 2^11 partials for its consumers to add
+        // tiles per item: 1 until the level has 24 items per CU (six rounds of the
+        // four workgroups a CU holds), then more, so that an item's next tile is
+        // in flight during its current one; 16 at most, but enough that a pass
+        // leaves at most 2^11 partials for its consumers to add.  Few long items
+        // leave the last round nearly empty: with 6 per CU, 256 states took 16.6
+        // ms for their passes, with 24 14.6 (64 states 4.3 and 4.2).
         uint64_t per_level = 1;
-        while (per_level < 16 && tiles / (2 * per_level) >= 6 * cus) per_level *= 2;
+        while (per_level < 16 && tiles / (2 * per_level) >= 24 * cus) per_level *= 2;
         struct Cost {
             double c;
             PassItem it;
