@@ -13,7 +13,7 @@
 // invalidate the XCD's L2, and waiting workgroups go on doing so.  64 states
 // of 12..21 qubits (8 layers, 200 terms each, k_max 4, 12-qubit tiles) took 84
 // ms for their passes and 8 ms for the energies, 4 states no less; as levels
-// they take 4.5 ms (26 launches of 173 us on average) and 2.2 ms, 4 states 0.8 ms.
+// they take 4.2 ms (26 launches of 162 us on average) and 2.1 ms, 4 states 0.8 ms.
 //
 // The renormalisation scale of pass p is the fixed-order FP64 sum of pass
 // p-1's item partials, recomputed by every consumer, so all of them see the

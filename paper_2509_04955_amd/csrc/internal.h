@@ -183,7 +183,7 @@ struct qs_plan_s {
     size_t pool_bytes[2] = {0, 0};
     std::vector<qs::BlockDev> h_blocks[2];
     std::vector<uint8_t> pass_wide[2];  // pass needs the wide kernel variant
-    std::vector<uint8_t> pass_lean[2];  // staged pass that a lean variant can run
+    std::vector<uint8_t> pass_lean[2];  // lean variant of a staged pass: 0 none, 1 a workgroup per tile only, 2 always
     // pool range of the pass's block operands staged in LDS (len 0 = none)
     std::vector<int32_t> pass_cl_off[2], pass_cl_len[2];
     ~qs_plan_s();

@@ -1197,16 +1197,25 @@ bool lean_enabled() {
 
 // Whether a staged pass (its operands take `bytes`) can run a lean variant:
 // 2^12-amplitude tiles, blocks within the variant's widths, and for complex64
-// operands that leave room for the fourth workgroup of a CU.
-bool lean_pass(const std::vector<HBlock> &blocks, const HPass &ps, qs_dtype dt, size_t bytes) {
-    if (!lean_enabled() || ps.t != 12) return false;
-    if (dt == QS_C64 && (8u << 12) + kRedBytes + bytes > 40 * 1024) return false;
+// operands that leave room for the fourth workgroup of a CU.  0: it cannot;
+// 1: only with a workgroup per tile; 2: also when workgroups take tile after
+// tile.  There a complex64 pass of few blocks is bound by memory, and the
+// general variant's deeper prefetch is worth more than the fourth workgroup.
+// Passes of 2^26 amplitudes, lean against general: 2 blocks 252 us against
+// 243, 4 class or permutation blocks 252 against 244; 5 blocks of 3 qubits 300
+// against 318, 6 mixed ones of 4 qubits 293 against 310; 2^28 amplitudes, 4
+// dense blocks 903 against 950.
+int lean_pass(const std::vector<HBlock> &blocks, const HPass &ps, qs_dtype dt, size_t bytes) {
+    if (!lean_enabled() || ps.t != 12) return 0;
+    if (dt == QS_C64 && (8u << 12) + kRedBytes + bytes > 40 * 1024) return 0;
+    int dense = 0;
     for (int64_t b = ps.block0; b < ps.block0 + ps.nblocks; ++b) {
         const int k = (int)blocks[b].qubits.size();
         const int kind = block_kind(blocks[b], ps.t, dt, nullptr, true);
-        if (dt == QS_C64 ? (kind == BK_MFMA || kind == BK_MONO) && k > 4 : kind == BK_PAULI || k > 3) return false;
+        if (dt == QS_C64 ? (kind == BK_MFMA || kind == BK_MONO) && k > 4 : kind == BK_PAULI || k > 3) return 0;
+        dense += kind == BK_MFMA;
     }
-    return true;
+    return dt == QS_C128 || ps.nblocks >= 5 || dense >= 4 ? 2 : 1;
 }
 }  // namespace
 
@@ -1330,11 +1339,11 @@ struct PassLaunch {
 qs_status pass_launch(const qs_state_s &s, const qs_plan_s &p, const HPass &ps, int64_t pass_index, PassLaunch &L) {
     const int di = s.dtype == QS_C64 ? 0 : 1;
     const bool wide = p.pass_wide[di][pass_index] != 0, cl = p.pass_cl_len[di][pass_index] > 0;
-    const bool lean = p.pass_lean[di][pass_index] != 0;
     const size_t amp = s.dtype == QS_C64 ? 8 : 16;
     L.ntiles = 1ull << (s.n - ps.t);
     for (const bool one : {true, false}) {
         bool static_tile = false;
+        const bool lean = p.pass_lean[di][pass_index] >= (one ? 1 : 2);
         L.k32 = nullptr;
         L.k64 = nullptr;
         if (s.dtype == QS_C64)

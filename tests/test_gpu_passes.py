@@ -52,6 +52,25 @@ def test_pass_chain(Q, oracle, dtype, n, k, t, renorm):
     assert abs(norm - (1.0 if renorm else 9.0)) <= 100 * TOL[dtype]
 
 
+@pytest.mark.parametrize("k,low", [(3, 4), (4, 6)])
+def test_staged_passes_light_and_heavy(Q, oracle, k, low):
+    """Staged complex64 passes on more tiles than fit at once, where the
+    number of blocks picks the variant: plans with passes on both sides."""
+    n = 23
+    c = qsynth.brickwork(n, 4, seed=k)
+    plan = Q.qs_contract(n, Q.GateList(c), Q.opts(k_max=k, tile_qubits=12, low_qubits=low, dtype=0))
+    counts = [Q.qs_plan_pass(plan, i)[3] for i in range(Q.qs_plan_info_get(plan).n_passes)]
+    assert min(counts) < 4 and (k == 4 or max(counts) > 4)
+    psi0 = qsynth.random_state(n, 5)
+    st = Q.State(n, 0)
+    st.load(psi0)
+    st.apply_plan(plan)
+    got = st.amplitudes()
+    st.close()
+    Q.qs_plan_destroy(plan)
+    assert oracle.max_abs(oracle.run(c, psi0), got) <= TOL[0]
+
+
 def test_captured_small_plan_replays(Q):
     """A plan whose passes give every tile a workgroup draws no tickets, so a
     captured launch can be replayed: each replay, with eager work between,
