@@ -124,6 +124,7 @@ qs_status run_expect(qs_state_s &s, const ExpectPlan &plan, void *d_scr, std::ve
 
 // the same in the state's own workspace
 qs_status run_expect_kept(qs_state_s &s, const ExpectPlan &plan, std::vector<double> &res) {
+    std::lock_guard<std::mutex> lk(s.expect_mu);
     // every call ends synchronised: nothing on the stream uses the buffers now
     const size_t need = expect_scratch_bytes(plan), host = expect_host_bytes(plan);
     // Pinned memory costs its allocation back only after a few calls (about 35
@@ -146,12 +147,14 @@ qs_status run_expect_kept(qs_state_s &s, const ExpectPlan &plan, std::vector<dou
     double *out = nullptr;
     void *pinned = s.expect_host_cap >= host ? s.h_expect : nullptr;
     const qs_status st = launch_expect(s, plan, s.d_expect, pinned, &out);
+    hipError_t e = hipSuccess;
     if (st == QS_OK && !pinned)
-        QS_HIP(hipMemcpyAsync(res.data(), out, res.size() * sizeof(double), hipMemcpyDeviceToHost, s.stream));
+        e = hipMemcpyAsync(res.data(), out, res.size() * sizeof(double), hipMemcpyDeviceToHost, s.stream);
     // after a failure too: work may be queued on the buffers
-    const hipError_t e = hipStreamSynchronize(s.stream);
+    const hipError_t e2 = hipStreamSynchronize(s.stream);
     if (st != QS_OK) return st;
-    if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize(expectation)");
+    if (e == hipSuccess) e = e2;
+    if (e != hipSuccess) return hip_fail(e, "expectation");
     if (pinned) std::copy_n(out, res.size(), res.begin());
     return QS_OK;
 }

@@ -125,7 +125,10 @@ struct qs_state_s {
     bool scale_pending = false;
     // expectation workspace, kept between calls and grown to the largest (at
     // most 4096 terms per launch: about 10 MB): device tables and partials,
-    // pinned host memory for the tables on their way and the results
+    // pinned host memory for the tables on their way and the results.  Reading
+    // an energy leaves the state as it is, so several threads may do so at once:
+    // the lock keeps one call's tables and results from the next one's.
+    std::mutex expect_mu;
     void *d_expect = nullptr;
     size_t expect_cap = 0;
     void *h_expect = nullptr;

@@ -24,3 +24,42 @@ def test_kept_workspace(oracle, dtype, tol):
         assert np.max(np.abs(t[::17] - ref)) <= tol
         assert abs(e - float(ham.coeff @ t)) <= 1e-12 * max(1.0, float(np.abs(ham.coeff) @ np.abs(t)))
     st.close()
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_threads_read_one_state(dtype):
+    """Threads that read energies of one state at once, each with its own
+    Hamiltonian and with sums that make the workspace grow between theirs, get
+    what one thread alone gets, bit for bit."""
+    import threading
+
+    import torch
+
+    from paper_2509_04955_amd import qsim as Q
+
+    n = 15
+    st = Q.State(n, dtype)
+    st.load(qsynth.random_state(n, seed=3))
+    hams = [[qsynth.random_pauli_sum(n, terms, seed=(w, terms)) for terms in (5 + w, 90 + 40 * w, 700 + 900 * w)]
+            for w in range(3)]
+    ref = Q.State(n, dtype)
+    ref.load(qsynth.random_state(n, seed=3))
+    want = [[ref.expect(h, with_terms=True) for h in hs] for hs in hams]
+    wrong = []
+
+    def read(w):
+        torch.cuda.set_device(0)
+        for _ in range(10):
+            for h, (e0, t0) in zip(hams[w], want[w]):
+                e, t = st.expect(h, with_terms=True)
+                if e != e0 or not np.array_equal(t, t0):
+                    wrong.append((w, len(h.coeff), e, e0))
+
+    threads = [threading.Thread(target=read, args=(w,)) for w in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    st.close()
+    ref.close()
+    assert not wrong, wrong[:4]
