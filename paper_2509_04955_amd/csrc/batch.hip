@@ -263,8 +263,11 @@ BatchKernel<R> batch_kernel(bool wide) {
 template <typename R>
 void enqueue_levels(const qs_batch_s &b, hipStream_t st) {
     for (const qs_batch_s::Level &lv : b.levels)
-        hipLaunchKernelGGL(batch_kernel<R>(lv.wide), dim3(lv.count), dim3(TT), lv.lds, st, b.d_items + lv.first,
-                           b.d_passes, b.d_blocks, (const R *)b.d_pools, (unsigned char *)b.d_amps, b.d_partials);
+        for (uint32_t i = 0, m; i < lv.count; i += m) {
+            m = std::min(lv.count - i, kMaxBatchGrid);
+            hipLaunchKernelGGL(batch_kernel<R>(lv.wide), dim3(m), dim3(TT), lv.lds, st, b.d_items + lv.first + i,
+                               b.d_passes, b.d_blocks, (const R *)b.d_pools, (unsigned char *)b.d_amps, b.d_partials);
+        }
 }
 
 qs_status enqueue_batch(qs_batch_s &b, hipStream_t st) {
@@ -439,6 +442,7 @@ qs_status qs_batch_create(int n_states, const int *n_qubits, const qs_gate *cons
             lv.wide |= p.pass_wide[di][pi] != 0;
             pdv.push_back(d);
         }
+        QS_CHECK(items.size() + level.size() <= UINT32_MAX, QS_ERANGE, "batch has more than 2^32 pass items");
         std::stable_sort(level.begin(), level.end(), [](const Cost &x, const Cost &y) { return x.c > y.c; });
         for (const Cost &c : level) items.push_back(c.it);
         lv.count = (uint32_t)(items.size() - lv.first);
@@ -508,6 +512,7 @@ qs_status qs_batch_create(int n_states, const int *n_qubits, const qs_gate *cons
             for (uint32_t c = 0; c < j.chunks; ++c)
                 (ep.small ? small : full).push_back(ExpectItem{(uint32_t)i, g, c, 0});
     }
+    QS_CHECK(full.size() + small.size() <= UINT32_MAX, QS_ERANGE, "batch has more than 2^32 energy items");
     b->n_full = (uint32_t)full.size();
     b->n_small = (uint32_t)small.size();
     full.insert(full.end(), small.begin(), small.end());

@@ -323,6 +323,9 @@ struct ExpectJob {
     int32_t l, D, b, log_cosets;
     uint32_t per_item, chunks, n_terms, pad;
 };
+// Workgroups of one launch of a batch, which has one per item: a grid holds
+// fewer than 2^32 threads, and an energy item has 1024.
+constexpr uint32_t kMaxBatchGrid = 1u << 20;
 struct ExpectItem {
     uint32_t job, group, chunk, pad;
 };
@@ -337,7 +340,8 @@ struct ExpectJobs {
     const ExpectItem *items;     // n_full items of states that hold a full coset, then n_small of smaller ones
     uint32_t n_full, n_small;
 };
-// energies receives one value per job
+// energies receives one value per job; items beyond kMaxBatchGrid take
+// further launches
 void launch_expect_jobs(hipStream_t st, qs_dtype dt, const ExpectJobs &j, double *energies);
 size_t expect_scratch_bytes(const ExpectPlan &p);
 // pinned host bytes of a launch: a copy of the tables, then the results

@@ -700,9 +700,11 @@ qs_status launch_expect(qs_state_s &s, const ExpectPlan &p, void *d_scratch, voi
 
 void launch_expect_jobs(hipStream_t st, qs_dtype dt, const ExpectJobs &j, double *energies) {
     auto run = [&](auto kernel, int threads, const ExpectItem *items, uint32_t count) {
-        if (count)
-            hipLaunchKernelGGL(kernel, dim3(count), dim3(threads), 0, st, (const unsigned char *)j.amps, j.jobs, items,
+        for (uint32_t i = 0, m; i < count; i += m) {
+            m = std::min(count - i, kMaxBatchGrid);
+            hipLaunchKernelGGL(kernel, dim3(m), dim3(threads), 0, st, (const unsigned char *)j.amps, j.jobs, items + i,
                                j.groups, j.terms, j.parts);
+        }
     };
     if (dt == QS_C64) {
         run(k_expect_jobs<cf2, kExpCosetBits64, kExpThreads, kExpAmps64, false>, kExpThreads, j.items, j.n_full);

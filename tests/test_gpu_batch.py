@@ -115,3 +115,45 @@ def test_batch_item_and_coset_edges(Q, oracle, dtype, tol):
         assert abs(E[i] - e) <= tol * max(1, abs(e)), (i, c.n, E[i], e)
         assert oracle.max_abs(psi, b.amplitudes(i)) <= (1e-5 if dtype == 0 else 1e-12)
     b.close()
+
+
+def test_batch_more_energy_items_than_one_grid(Q):
+    """A 26-qubit complex128 state with 65536 terms has 2^22 energy items and
+    more, of 1024 threads each, where a grid holds fewer than 2^32 threads.
+    The state is a product of RY rotations and the terms have X and Z letters,
+    so every expectation is a product of sines and cosines.  Rounding: 2^26
+    summands of at most 2^-26 in FP64 give each term to about 1e-14."""
+    n, terms = 26, 65536
+    rng = np.random.default_rng(12)
+    theta = rng.uniform(0.5, 1.0, size=n)
+    c = qsynth.Circuit(n)
+    for q in range(n):
+        c.add("ry", (q,), (theta[q],))
+    letters = rng.integers(0, 3, size=(terms, n))   # I, X, Z
+    bits = (np.uint64(1) << np.arange(n, dtype=np.uint64))
+    x = ((letters == 1) * bits).sum(axis=1, dtype=np.uint64)
+    z = ((letters == 2) * bits).sum(axis=1, dtype=np.uint64)
+    want = np.prod(np.where(letters == 1, np.sin(theta), np.where(letters == 2, np.cos(theta), 1.0)), axis=1)
+    coeff = rng.normal(size=terms)
+    b = Q.Batch([c], [qsynth.PauliSum(n, x, z, coeff)], Q.opts(k_max=3, tile_qubits=12, low_qubits=4, dtype=1))
+    e = b.run()[0]
+    b.close()
+    assert abs(e - coeff @ want) <= 1e-13 * np.abs(coeff).sum()
+
+
+def test_batch_more_pass_items_than_one_launch(Q):
+    """600 states of 19 qubits in four-qubit tiles: 2048 items each, more in a
+    level than one launch takes."""
+    n, states = 19, 600
+    theta = np.linspace(0.2, 2.9, states)
+    circuits = [qsynth.Circuit(n).add("ry", (i % n,), (theta[i],)) for i in range(states)]
+    hams = [qsynth.PauliSum(n, np.zeros(1, np.uint64), np.array([1 << (i % n)], np.uint64), np.ones(1))
+            for i in range(states)]
+    b = Q.Batch(circuits, hams, Q.opts(k_max=1, tile_qubits=4, low_qubits=2))
+    e = b.run()
+    assert np.max(np.abs(e - np.cos(theta))) <= 1e-6
+    for i in (0, 511, 512, states - 1):
+        want = np.zeros(1 << n, dtype=np.complex128)
+        want[0], want[1 << (i % n)] = np.cos(theta[i] / 2), np.sin(theta[i] / 2)
+        assert np.max(np.abs(b.amplitudes(i) - want)) <= 1e-6
+    b.close()
