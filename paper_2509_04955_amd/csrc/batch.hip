@@ -459,7 +459,7 @@ qs_status qs_batch_create(int n_states, const int *n_qubits, const qs_gate *cons
             set_error("batch kernel declares static LDS: its tile would not sit at LDS address 0");
             return fail(QS_EDEVICE);
         }
-        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        e = set_dynamic_lds(fn, lds);   // never lowered: other batches' graphs use the kernel too
         if (e != hipSuccess) return fail(hip_fail(e, "hipFuncSetAttribute(batch)"));
     }
     // ---- energies: one job per state, items = runs of cosets of a term group ----

@@ -157,3 +157,14 @@ def test_batch_more_pass_items_than_one_launch(Q):
         want[0], want[1 << (i % n)] = np.cos(theta[i] / 2), np.sin(theta[i] / 2)
         assert np.max(np.abs(b.amplitudes(i) - want)) <= 1e-6
     b.close()
+
+
+def test_batch_tiles_of_several_sizes(Q, oracle):
+    """A batch keeps its LDS room when one with smaller tiles is made after it."""
+    circuits = [qsynth.hea(n, 3, seed=(8, n)) for n in (14, 15)]
+    hams = [qsynth.random_pauli_sum(c.n, 10, seed=(8, c.n)) for c in circuits]
+    batches = [Q.Batch(circuits, hams, Q.opts(k_max=3, tile_qubits=t, low_qubits=4)) for t in (14, 13, 10)]
+    want = [_oracle_energy(oracle, c, h)[1] for c, h in zip(circuits, hams)]
+    for b in batches:
+        assert np.max(np.abs(b.run() - want)) <= 1e-5
+        b.close()
