@@ -312,6 +312,9 @@ qs_status qs_batch_create(int n_states, const int *n_qubits, const qs_gate *cons
     auto fail = [](qs_status s) { return s; };
     // ---- plans (autotuned per qubit count when k_max or tile is 0) ----
     std::map<int, qs_contract_opts> tuned;
+    std::vector<unsigned char> pools, image;   // every plan's operands
+    std::vector<size_t> pool0(n_states);
+    const int di = dt == QS_C64 ? 0 : 1;
     for (int i = 0; i < n_states; ++i) {
         qs_contract_opts o = base;
         o.dtype = dt;
@@ -342,8 +345,11 @@ qs_status qs_batch_create(int n_states, const int *n_qubits, const qs_gate *cons
         }
         b->plans.push_back(p);
         b->n.push_back(n_qubits[i]);
-        st = plan_upload(*p, dt, false);
+        st = plan_image(*p, dt, false, image);
         if (st != QS_OK) return fail(st);
+        pool0[i] = pools.size();
+        pools.insert(pools.end(), image.begin(), image.begin() + (int64_t)p->pool_bytes[di]);
+        pools.resize((pools.size() + 255) / 256 * 256);
     }
     // ---- device layout ----
     const size_t ab = dt == QS_C64 ? 8 : 16;
@@ -370,29 +376,19 @@ qs_status qs_batch_create(int n_states, const int *n_qubits, const qs_gate *cons
     if (e == hipSuccess) e = hipGetDeviceProperties(&prop, dev);
     if (e != hipSuccess) return fail(hip_fail(e, "device properties"));
     const uint64_t cus = std::max(1, prop.multiProcessorCount);
-    const int di = dt == QS_C64 ? 0 : 1;
     // one table of blocks and one of operands: kernel arguments, so that the
     // wave-uniform reads of block records and matrices are scalar loads
     std::vector<BlockDev> blocks;
-    std::vector<size_t> block0(n_states), pool0(n_states);
-    size_t pool_bytes = 0;
+    std::vector<size_t> block0(n_states);
     for (int i = 0; i < n_states; ++i) {
         const qs_plan_s &p = *b->plans[i];
         block0[i] = blocks.size();
         blocks.insert(blocks.end(), p.h_blocks[di].begin(), p.h_blocks[di].end());
-        pool0[i] = pool_bytes;
-        pool_bytes += (p.pool_bytes[di] + 255) / 256 * 256;
     }
     QS_CHECK(blocks.size() <= 0x7fffffffu, QS_ERANGE, "batch has more than 2^31 blocks");
     qs_status st = upload(&b->d_blocks, blocks);
+    if (st == QS_OK) st = upload((unsigned char **)&b->d_pools, pools);
     if (st != QS_OK) return fail(st);
-    e = hipMalloc(&b->d_pools, std::max<size_t>(pool_bytes, 16));
-    for (int i = 0; i < n_states && e == hipSuccess; ++i)
-        if (b->plans[i]->pool_bytes[di])
-            e = hipMemcpyAsync((unsigned char *)b->d_pools + pool0[i], b->plans[i]->d_pool[di],
-                               b->plans[i]->pool_bytes[di], hipMemcpyDeviceToDevice, nullptr);
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    if (e != hipSuccess) return fail(hip_fail(e, "batch operands"));
     std::vector<PassDev> pdv;
     std::vector<PassItem> items;
     b->last.assign(n_states, qs_batch_s::LastPass{0, 0});

@@ -200,9 +200,13 @@ qs_status make_gate(const qs_gate &g, int n, HGate &out);
 // planner.cpp
 qs_status build_plan(qs_plan_s &p);
 void block_matrix(const std::vector<HGate> &gates, HBlock &b);
-// stage_lds: let passes stage their block operands in LDS (the single-state
-// pass kernel); the batch kernel reads them from the pool.
-qs_status plan_upload(qs_plan_s &p, qs_dtype dt, bool stage_lds = true);
+// kernels_tile.hip: device copy of a plan's operands and block records
+qs_status plan_upload(qs_plan_s &p, qs_dtype dt);
+// what plan_upload copies: the operands (pool_bytes of them), then the block
+// records (h_blocks holds them too).  stage_lds: passes may stage their
+// operands in LDS (the single-state pass kernel); the batch kernel reads them
+// from the pool.
+qs_status plan_image(qs_plan_s &p, qs_dtype dt, bool stage_lds, std::vector<unsigned char> &image);
 // kernels_tile.hip: how the tile kernel will apply a block (BK_*); dest gets
 // the monomial destinations when the block is monomial; lds: the pass stages
 // its operands in LDS (dense complex64 k = 3 then also runs on MFMA)

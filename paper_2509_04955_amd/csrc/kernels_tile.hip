@@ -1183,7 +1183,10 @@ bool pass_staged(const std::vector<HBlock> &blocks, const HPass &ps, qs_dtype dt
 }
 
 namespace {
-qs_status plan_upload_impl(qs_plan_s &p, qs_dtype dt, bool stage_lds);
+qs_status build_image(qs_plan_s &p, qs_dtype dt, bool stage_lds, std::vector<unsigned char> &image);
+
+// where the block records lie in a plan's image, behind its operands
+size_t blocks_offset(size_t pool_bytes) { return (pool_bytes + 255) / 256 * 256; }
 
 // QS_TILE_LEAN=0: staged passes keep the general variants
 bool lean_enabled() {
@@ -1221,9 +1224,9 @@ int lean_pass(const std::vector<HBlock> &blocks, const HPass &ps, qs_dtype dt, s
 
 // Host invariants of the records (a rotation's X part inside its tile, a
 // group's independent X parts) throw; no exception leaves through the ABI.
-qs_status plan_upload(qs_plan_s &p, qs_dtype dt, bool stage_lds) {
+qs_status plan_image(qs_plan_s &p, qs_dtype dt, bool stage_lds, std::vector<unsigned char> &image) {
     try {
-        return plan_upload_impl(p, dt, stage_lds);
+        return build_image(p, dt, stage_lds, image);
     } catch (const std::bad_alloc &) {
         set_error("host allocation failed while uploading a plan");
         return QS_ENOMEM;
@@ -1233,10 +1236,23 @@ qs_status plan_upload(qs_plan_s &p, qs_dtype dt, bool stage_lds) {
     }
 }
 
-namespace {
-qs_status plan_upload_impl(qs_plan_s &p, qs_dtype dt, bool stage_lds) {
+qs_status plan_upload(qs_plan_s &p, qs_dtype dt) {
     const int di = dt == QS_C64 ? 0 : 1;
     if (p.dev_ready[di]) return QS_OK;
+    std::vector<unsigned char> image;
+    const qs_status st = plan_image(p, dt, true, image);
+    if (st != QS_OK) return st;
+    // one allocation and one copy
+    QS_HIP(hipMalloc(&p.d_pool[di], image.size()));
+    QS_HIP(hipMemcpy(p.d_pool[di], image.data(), image.size(), hipMemcpyHostToDevice));
+    p.d_blocks[di] = reinterpret_cast<BlockDev *>((unsigned char *)p.d_pool[di] + blocks_offset(p.pool_bytes[di]));
+    p.dev_ready[di] = 1;
+    return QS_OK;
+}
+
+namespace {
+qs_status build_image(qs_plan_s &p, qs_dtype dt, bool stage_lds, std::vector<unsigned char> &image) {
+    const int di = dt == QS_C64 ? 0 : 1;
     std::vector<BlockDev> hb(p.blocks.size());
     std::vector<float> pool32;
     std::vector<double> pool64;
@@ -1294,18 +1310,12 @@ qs_status plan_upload_impl(qs_plan_s &p, qs_dtype dt, bool stage_lds) {
         }
     }
     p.h_blocks[di] = hb;
-    // one allocation and one copy: the operands, then the block records
     const size_t pbytes = dt == QS_C64 ? pool32.size() * sizeof(float) : pool64.size() * sizeof(double);
-    const size_t boff = (pbytes + 255) / 256 * 256, total = boff + std::max<size_t>(1, hb.size()) * sizeof(BlockDev);
-    std::vector<unsigned char> image(total);
+    image.resize(blocks_offset(pbytes) + std::max<size_t>(1, hb.size()) * sizeof(BlockDev));
     if (pbytes)
         std::memcpy(image.data(), dt == QS_C64 ? (const void *)pool32.data() : (const void *)pool64.data(), pbytes);
-    if (!hb.empty()) std::memcpy(image.data() + boff, hb.data(), hb.size() * sizeof(BlockDev));
-    QS_HIP(hipMalloc(&p.d_pool[di], total));
-    QS_HIP(hipMemcpy(p.d_pool[di], image.data(), total, hipMemcpyHostToDevice));
-    p.d_blocks[di] = reinterpret_cast<BlockDev *>((unsigned char *)p.d_pool[di] + boff);
+    if (!hb.empty()) std::memcpy(image.data() + blocks_offset(pbytes), hb.data(), hb.size() * sizeof(BlockDev));
     p.pool_bytes[di] = pbytes;
-    p.dev_ready[di] = 1;
     return QS_OK;
 }
 }  // namespace

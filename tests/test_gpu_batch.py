@@ -168,3 +168,29 @@ def test_batch_tiles_of_several_sizes(Q, oracle):
     for b in batches:
         assert np.max(np.abs(b.run() - want)) <= 1e-5
         b.close()
+
+
+def test_batch_holds_its_operands_once(Q):
+    """Device memory of a batch: one copy of the operands of all plans.  40
+    six-qubit dense gates in each of 20 states are 800 blocks of 64 KiB (the
+    128 x 128 real form), 52 MB; the states and tables are below 4 MB."""
+    import torch
+
+    rng = np.random.default_rng(3)
+    u, _ = np.linalg.qr(rng.normal(size=(64, 64)) + 1j * rng.normal(size=(64, 64)))
+    n, states, gates = 11, 20, 40
+    circuits = []
+    for i in range(states):
+        c = qsynth.Circuit(n)
+        for _ in range(gates):
+            c.add("dense", tuple(int(q) for q in rng.permutation(n)[:6]), matrix=u)
+        circuits.append(c)
+    hams = [qsynth.random_pauli_sum(n, 2, seed=(4, i)) for i in range(states)]
+    o = Q.opts(k_max=6, tile_qubits=11, low_qubits=2, strategy=Q.STRATEGY_NONE)
+    Q.Batch(circuits[:1], hams[:1], o).close()   # the first use of the kernels
+    free0, _ = torch.cuda.mem_get_info()
+    b = Q.Batch(circuits, hams, o)
+    used = free0 - torch.cuda.mem_get_info()[0]
+    b.close()
+    one = states * gates * 128 * 128 * 4
+    assert one <= used <= 1.5 * one, (used, one)
