@@ -155,8 +155,22 @@ class GateList:
                 m = np.ascontiguousarray(np.asarray(g.matrix, dtype=np.complex128)).view(np.float64).copy()
                 self._keep.append(m)
                 ptr = m.ctypes.data
-            pack(self.arr, at, KIND[g.name], len(q), *q, *pads[8 - len(q)], *p, *pads[4 - len(p)], ptr)
+            try:
+                pack(self.arr, at, KIND[g.name], len(q), *q, *pads[8 - len(q)], *p, *pads[4 - len(p)], ptr)
+            except struct.error:
+                self._put(at // 80, g, ptr)
             at += 80
+
+    def _put(self, i, g, ptr):
+        """Field by field, for a gate that struct refuses: what a gate record
+        has no room for raises, and a qubit is taken modulo 2^32 and left to
+        the library to judge."""
+        e = self.arr[i]
+        e.kind, e.nq, e.matrix = KIND[g.name], len(g.qubits), ptr or None
+        for j, v in enumerate(g.qubits):
+            e.qubits[j] = v
+        for j, v in enumerate(g.params):
+            e.params[j] = v
 
     @property
     def ptr(self):

@@ -522,3 +522,25 @@ def test_commute_with_every_strategy_replays_exactly(Q, oracle, strategy):
     ref = oracle.run(c, psi0.copy())
     got = greedy.apply_blocks(psi0.copy(), n, qls, mats)
     assert np.max(np.abs(got - ref)) < 1e-12
+
+
+def test_gate_list_out_of_range_values(Q):
+    """A gate list takes qubits as C integers and leaves them to the library;
+    what a record has no room for, or is no number, raises the error of its
+    field."""
+    def gates(name, qubits, params=()):
+        return qsynth.Circuit(3, [qsynth.Gate(name, qubits, params)])
+
+    gl = Q.GateList(gates("h", (2 ** 31,)))
+    assert gl.arr[0].qubits[0] == -2 ** 31
+    with pytest.raises(Q.QsimError) as ei:
+        Q.qs_contract(3, gl)
+    assert ei.value.status == Q.QS_EINVAL
+    assert Q.GateList(gates("rx", (2 ** 32 + 1,), (0.5,))).arr[0].qubits[0] == 1
+    for bad in (gates("h", tuple(range(9))), gates("u3", (0,), (1, 2, 3, 4, 5))):
+        with pytest.raises(IndexError):
+            Q.GateList(bad)
+    text = gates("rx", (0,), (0.5,))
+    text.gates[0].params = ("half",)
+    with pytest.raises(TypeError):
+        Q.GateList(text)
