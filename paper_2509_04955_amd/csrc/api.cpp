@@ -434,6 +434,7 @@ qs_status qs_plan_pass(qs_plan p, uint64_t i, int *t, int *tile_qubits, uint64_t
 }
 
 qs_status qs_apply_plan(qs_state s, qs_plan p) {
+    QS_ABI_TRY
     QS_CHECK(s && p, QS_EINVAL, "null argument");
     QS_CHECK(s->n == p->n, QS_EINVAL, "plan is for %d qubits, state has %d", p->n, s->n);
     const int tcap = s->dtype == QS_C128 ? kMaxTile128 : kMaxTile;
@@ -442,6 +443,7 @@ qs_status qs_apply_plan(qs_state s, qs_plan p) {
     qs_status st = plan_upload(*p, s->dtype);
     if (st != QS_OK) return st;
     return launch_plan(*s, *p);
+    QS_ABI_CATCH
 }
 
 qs_status qs_expect_pauli_sum(qs_state s, const uint64_t *x, const uint64_t *z, const double *coeff, size_t n_terms,
