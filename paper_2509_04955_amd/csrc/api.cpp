@@ -141,8 +141,12 @@ qs_status run_expect_kept(qs_state_s &s, const ExpectPlan &plan, std::vector<dou
         if (s.h_expect) QS_HIP(hipHostFree(s.h_expect));
         s.h_expect = nullptr;
         s.expect_host_cap = 0;
-        QS_HIP(hipHostMalloc(&s.h_expect, host, hipHostMallocDefault));
-        s.expect_host_cap = host;
+        if (hipHostMalloc(&s.h_expect, host, hipHostMallocDefault) == hipSuccess) {
+            s.expect_host_cap = host;
+        } else {   // no pinned memory left: pageable, as in a first sum
+            s.h_expect = nullptr;
+            (void)hipGetLastError();
+        }
     }
     double *out = nullptr;
     void *pinned = s.expect_host_cap >= host ? s.h_expect : nullptr;
