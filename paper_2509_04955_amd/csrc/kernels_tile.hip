@@ -532,6 +532,34 @@ TileKernel<R> pick_tile_kernel(bool wide, int t, bool cl, bool lean, int &thread
     return k_tile_pass<R, false, 0, false, TT, ONE>;
 }
 
+// Workgroups per CU of the staged variant for tiles of 2^t amplitudes, 0: none.
+constexpr int staged_groups(int t, qs_dtype dt) {
+    // complex64 2^13 tiles: 2 workgroups per CU (512 threads, or 256 with
+    // QS_TILE_BIG=0); 2^14 tiles are not staged (a staged 1024-thread variant
+    // spills registers at 4 waves per SIMD, and a reload waits for the prefetch)
+    if (dt == QS_C64) return t == 11 ? 4 : t == 12 ? 3 : t == 13 ? 2 : 0;
+    return t == 11 || t == 12 ? 2 : 0;   // complex128 variants run 2 workgroups per CU
+}
+
+// Whether the matrix-core blocks of 3..5 qubits cover every staged tile in
+// whole rounds, with the threads pick_tile_kernel gives it (complex64 2^13:
+// 512 or 256; complex128 2^12: 256, or 512 in the lean variant, whose widest
+// block has 3 qubits).
+template <typename R>
+constexpr bool staged_tiles_covered() {
+    const qs_dtype dt = sizeof(R) == 4 ? QS_C64 : QS_C128;
+    for (int t = 0; t <= kMaxTile; ++t)
+        if (staged_groups(t, dt))
+            for (int k = 3; k <= 5; ++k)
+                for (int nt = TT; nt <= 512; nt *= 2) {
+                    if (nt == 512 && !(dt == QS_C64 ? t == 13 : t == 12 && k == 3)) continue;
+                    const uint32_t rounds = t - k >= 4 ? staged_rounds<R>(t, k, nt) : 0;
+                    if (rounds < 1 || rounds > 8) return false;
+                }
+    return true;
+}
+static_assert(staged_tiles_covered<float>() && staged_tiles_covered<double>(), "staged tile without whole rounds");
+
 // LDS bytes a pass may use for staged operands: what is left of the CU's LDS
 // share per workgroup at the occupancy the staged variant targets (complex64
 // 2^11: 4, 2^12: 3, 2^13: 2 workgroups per CU; complex128 2^11, 2^12: 2),
@@ -539,12 +567,7 @@ TileKernel<R> pick_tile_kernel(bool wide, int t, bool cl, bool lean, int &thread
 // variant for this tile.
 size_t lds_operand_budget(int t, qs_dtype dt) {
     constexpr size_t kLds = 160 * 1024, kMargin = 512;
-    int wgs = 0;
-    // complex64 2^13 tiles: 2 workgroups per CU (512 threads, or 256 with
-    // QS_TILE_BIG=0); 2^14 tiles are not staged (a staged 1024-thread variant
-    // spills registers at 4 waves per SIMD, and a reload waits for the prefetch)
-    if (dt == QS_C64) wgs = t == 11 ? 4 : t == 12 ? 3 : t == 13 ? 2 : 0;
-    else wgs = t == 11 || t == 12 ? 2 : 0;   // complex128 variants run 2 workgroups per CU
+    const int wgs = staged_groups(t, dt);
     if (!wgs) return 0;
     const size_t share = (kLds / wgs) & ~(size_t)1023, tile = (size_t)(dt == QS_C64 ? 8 : 16) << t;
     return share > tile + kMargin ? share - tile - kMargin : 0;

@@ -176,6 +176,20 @@ __device__ __forceinline__ uint32_t pick_lane(uint32_t v, const uint32_t *__rest
 }
 constexpr int log2i(int v) { return v <= 1 ? 0 : 1 + log2i(v / 2); }
 
+// Chunks of 16 groups that a wave has in flight in a staged matrix-core block
+// of k qubits, and the rounds in which the waves of nt threads then cover a
+// tile of 2^t amplitudes.  The blocks have no path for a short round and
+// decode three bits of the round number: kernels_tile.hip asserts that every
+// staged tile gives 1..8 whole rounds.
+template <typename R>
+constexpr int staged_chunks(int k) {
+    return k >= 5 ? 1 : k == 3 && sizeof(R) == 4 ? 4 : 2;
+}
+template <typename R>
+__host__ __device__ constexpr uint32_t staged_rounds(int t, int k, int nt) {
+    return (1u << (t - k)) / (uint32_t)(16 * staged_chunks<R>(k) * (nt / 64));
+}
+
 // A 32-bit pattern stored in an operand pool entry (bit-cast, not converted).
 __device__ __forceinline__ uint32_t pool_bits(float v) { return __float_as_uint(v); }
 __device__ __forceinline__ uint32_t pool_bits(double v) { return (uint32_t)__double_as_longlong(v); }
@@ -722,7 +736,7 @@ __device__ __forceinline__ void mfma_block_lds(TL tl, int T, const BlockDev *bd,
     constexpr int MT = 2 * D / 16;
     constexpr int S = 2 * D / 4;
     constexpr int NB = D / 4;
-    constexpr int CPI = K >= 5 ? 1 : sizeof(R) == 4 ? 4 : 2;
+    constexpr int CPI = staged_chunks<R>(K);
     constexpr bool HOIST = K == 3;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -750,7 +764,7 @@ __device__ __forceinline__ void mfma_block_lds(TL tl, int T, const BlockDev *bd,
         for (int i = 0; i < MT * (S / 4); ++i) ah[i] = A4[i * 64 + lane];
     }
     constexpr int LC = log2i(CPI), LW = log2i(NT / 64);
-    const uint32_t rounds = (1u << (T - K)) / (16 * CPI * (NT / 64));
+    const uint32_t rounds = staged_rounds<R>(T, K, NT);
     const uint32_t hj = tl.grp(pick_lane<4>((uint32_t)jc, gb)) ^ pick_uniform<LW>((uint32_t)wave, gb + 4 + LC);
     for (uint32_t r = 0; r < rounds; ++r) {
         const uint32_t hr = hj ^ pick_uniform<3>(r, gb + 4 + LC + LW);
@@ -818,7 +832,7 @@ __device__ __forceinline__ void mfma3m_block_lds(TL tl, int T, const BlockDev *b
     constexpr int MT = D / 16;
     constexpr int S = D / 4;
     constexpr int S4 = S / 4;
-    constexpr int CPI = K >= 5 ? 1 : 2;
+    constexpr int CPI = staged_chunks<R>(K);
     constexpr bool HOIST = K == 4;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -849,7 +863,7 @@ __device__ __forceinline__ void mfma3m_block_lds(TL tl, int T, const BlockDev *b
                 for (int s4 = 0; s4 < S4; ++s4) ah[(g * MT + m) * S4 + s4] = A4[aidx(g, m, s4)];
     }
     constexpr int LC = log2i(CPI), LW = log2i(NT / 64);
-    const uint32_t rounds = (1u << (T - K)) / (16 * CPI * (NT / 64));
+    const uint32_t rounds = staged_rounds<R>(T, K, NT);
     const uint32_t hj = tl.grp(pick_lane<4>((uint32_t)jc, gb)) ^ pick_uniform<LW>((uint32_t)wave, gb + 4 + LC);
     for (uint32_t r = 0; r < rounds; ++r) {
         const uint32_t hr = hj ^ pick_uniform<3>(r, gb + 4 + LC + LW);
@@ -924,7 +938,7 @@ constexpr int kBdPackFloats = 256 + 8 + 8;
 template <int K, int NT = TT, typename TL>
 __device__ __forceinline__ void bdiag_mfma_block(TL tl, int T, const BlockDev *bd, const float *Es) {
     constexpr int NPK = (1 << K) / 8;
-    constexpr int CPI = 2;   // chunks in flight per wave
+    constexpr int CPI = staged_chunks<float>(K);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, jc = lane & 15;
@@ -945,7 +959,7 @@ __device__ __forceinline__ void bdiag_mfma_block(TL tl, int T, const BlockDev *b
         oo[p][1] = ob[1];
     }
     constexpr int LC = log2i(CPI), LW = log2i(NT / 64);
-    const uint32_t rounds = (1u << (T - K)) / (16 * CPI * (NT / 64));
+    const uint32_t rounds = staged_rounds<float>(T, K, NT);
     const uint32_t hj = tl.grp(pick_lane<4>((uint32_t)jc, gb)) ^ pick_uniform<LW>((uint32_t)wave, gb + 4 + LC);
     for (uint32_t r = 0; r < rounds; ++r) {
         const uint32_t hr = hj ^ pick_uniform<3>(r, gb + 4 + LC + LW);
