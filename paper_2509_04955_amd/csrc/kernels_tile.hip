@@ -230,10 +230,29 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT, LEAN>())) void
         const uint64_t base = tile_base(blockIdx.x, pa);
         constexpr int LD = NJ > 0 ? NJ : kPrefetch;   // vectors loaded at once
         V v[LD];
+        // A fixed tile's vector addresses come from the masks of j's bits: kept
+        // one by one over the blocks, they spilled (see the marker below).
+        constexpr int LJ = log2i(LD);
+        uint64_t gb[LJ > 0 ? LJ : 1] = {};
+        if constexpr (NJ > 0) {
+#pragma unroll
+            for (int i = 0; i < LJ; ++i) gb[i] = tile_offset((NT * APV) << i, pa);
+        }
+        auto vec = [&](uint32_t j0, int j) -> V * {
+            if constexpr (NJ > 0) {
+                uint64_t o = 0;
+#pragma unroll
+                for (int i = 0; i < LJ; ++i)
+                    if ((j >> i) & 1) o |= gb[i];
+                return reinterpret_cast<V *>(psi + (base | g_t | o));
+            } else {
+                return gaddr(base, j0 + (uint32_t)j);
+            }
+        };
         auto load = [&](uint32_t j0) {
 #pragma unroll
             for (int j = 0; j < LD; ++j)
-                if (NJ > 0 || (active && j0 + j < nj)) v[j] = *gaddr(base, j0 + j);
+                if (NJ > 0 || (active && j0 + j < nj)) v[j] = *vec(j0, j);
         };
         auto put = [&](uint32_t j0) {
 #pragma unroll
@@ -271,6 +290,9 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT, LEAN>())) void
             apply_block<R, WIDE, CL, NT, true, LEAN>(tl, T, blocks + pa.block0 + b, pool, base, cst, pa.cl_off);
             __syncthreads();
         }
+        // the store's addresses are formed anew from here on
+#pragma unroll
+        for (int i = 0; i < LJ; ++i) asm volatile("" : "+s"(gb[i]));
         double nacc = 0.0;
         for (uint32_t j0 = 0; j0 < nj; j0 += LD) {
 #pragma unroll
@@ -280,7 +302,7 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT, LEAN>())) void
 #pragma unroll
             for (int j = 0; j < LD; ++j)
                 if (NJ > 0 || (active && j0 + j < nj)) {
-                    *gaddr(base, j0 + j) = v[j];
+                    *vec(j0, j) = v[j];
                     nacc += norm_of(v[j]);
                 }
         }
