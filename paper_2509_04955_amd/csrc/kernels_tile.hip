@@ -287,7 +287,7 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT, LEAN>())) void
         __syncthreads();
         for (int b = 0; b < pa.nblocks; ++b) {
             if (blocks[pa.block0 + b].kind == BK_SKIP) continue;   // folded into a group (uniform)
-            apply_block<R, WIDE, CL, NT, true, LEAN>(tl, T, blocks + pa.block0 + b, pool, base, cst, pa.cl_off);
+            apply_block<R, WIDE, CL, NT, true, LEAN, ONE>(tl, T, blocks + pa.block0 + b, pool, base, cst, pa.cl_off);
             __syncthreads();
         }
         // the store's addresses are formed anew from here on

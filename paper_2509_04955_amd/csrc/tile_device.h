@@ -306,7 +306,7 @@ __device__ __forceinline__ void valu_block(TL tl, int T, const BlockDev *bd, con
 // one wave (LPG = 1 for K <= 3, 2^(K-3) above), each holding 8 or fewer
 // sources; the lanes of a wave issue all their LDS reads before any write, so
 // the in-place permutation is safe.
-template <int K, typename R, int NT = TT, typename TL>
+template <int K, typename R, int NT = TT, bool FENCE = false, typename TL>
 __device__ __forceinline__ void mono_block(TL tl, int T, const BlockDev *bd, const R *__restrict__ E) {
     using A = typename AmpOf<R>::A;
     constexpr int LPG = K <= 3 ? 1 : (1 << (K > 3 ? K - 3 : 0));
@@ -333,6 +333,9 @@ __device__ __forceinline__ void mono_block(TL tl, int T, const BlockDev *bd, con
         A v[SPL];
 #pragma unroll
         for (int i = 0; i < SPL; ++i) v[i] = *tl.template at<A>(hs, sw(deposit((uint32_t)i)) * (uint32_t)sizeof(A));
+        // FENCE: the entries are scalar loads that may still be in flight; a use
+        // of one moved up here would hold back the reads
+        if constexpr (FENCE) reads_first();
         const uint32_t hd = tl.grp(sw(b) * (uint32_t)sizeof(A));
         // entry c = p * SPL + i: wave-uniform (scalar loads) when LPG == 1
         const R *Ep = E + 4 * (p * SPL);
@@ -1086,7 +1089,8 @@ __device__ __forceinline__ void class_mfma_block(TL tl, int T, const BlockDev *b
 // LEAN (staged passes): complex64 without dense or monomial blocks wider than 4
 // qubits, complex128 without rotations and without any block wider than 3:
 // their paths need registers that cost a wave.
-template <typename R, bool WIDE, bool CL = false, int NT = TT, bool PG = true, bool LEAN = false, typename TL>
+template <typename R, bool WIDE, bool CL = false, int NT = TT, bool PG = true, bool LEAN = false, bool ONE = false,
+          typename TL>
 __device__ __forceinline__ void apply_block(TL tile, int T, const BlockDev *bd,
                                             const R *__restrict__ pool, uint64_t gbase, const R *cst = nullptr,
                                             int cl_off = 0) {
@@ -1101,9 +1105,9 @@ __device__ __forceinline__ void apply_block(TL tile, int T, const BlockDev *bd,
             if (bd->sub == 1) bdiag_block<3, 1, R, NT>(tile, T, bd, U);
             else bdiag_block<3, 2, R, NT>(tile, T, bd, U);
         } else if (kind == BK_MONO) {
-            if (k == 1) mono_block<1, R, NT>(tile, T, bd, U);
-            else if (k == 2) mono_block<2, R, NT>(tile, T, bd, U);
-            else mono_block<3, R, NT>(tile, T, bd, U);
+            if (k == 1) mono_block<1, R, NT, ONE>(tile, T, bd, U);
+            else if (k == 2) mono_block<2, R, NT, ONE>(tile, T, bd, U);
+            else mono_block<3, R, NT, ONE>(tile, T, bd, U);
         } else {
             if (k == 1) valu_block<1, R, NT>(tile, T, bd, U);
             else if (k == 2) valu_block<2, R, NT>(tile, T, bd, U);
@@ -1172,9 +1176,9 @@ __device__ __forceinline__ void apply_block(TL tile, int T, const BlockDev *bd,
     }
     if (kind == BK_MONO) {
         switch (k) {
-        case 1: mono_block<1, R, NT>(tile, T, bd, U); return;
-        case 2: mono_block<2, R, NT>(tile, T, bd, U); return;
-        case 3: mono_block<3, R, NT>(tile, T, bd, U); return;
+        case 1: mono_block<1, R, NT, ONE>(tile, T, bd, U); return;
+        case 2: mono_block<2, R, NT, ONE>(tile, T, bd, U); return;
+        case 3: mono_block<3, R, NT, ONE>(tile, T, bd, U); return;
         default: break;
         }
         if constexpr (CL) {
