@@ -79,14 +79,26 @@ struct BlockDev {
     int32_t mat_off;    // offset (reals) of the matrix data in the plan's pool
     int32_t sub;        // BK_BDIAG: log2 of the class width, else 0
     int32_t pos[kMaxK]; // tile positions (ascending) of the block's qubits
-    // LDS byte offsets (swizzled) that the tile's index bits move an amplitude
-    // by, for the matrix-core paths: of the block's own qubits, and of bit i of
-    // a group number (its i-th free tile position; 0 beyond the last)
-    uint32_t pbit[kMaxK];
-    uint32_t gbit[12];
-    int32_t pad2[4];
 };
-static_assert(sizeof(BlockDev) == 128, "BlockDev layout");
+static_assert(sizeof(BlockDev) == 40, "BlockDev layout");
+// LDS byte offsets (swizzled) that the tile's index bits move an amplitude by,
+// for the staged matrix-core blocks: of the block's own qubits, and of bit i
+// of a group number (its i-th free tile position; 0 beyond the last).
+struct BlockBits {
+    uint32_t pbit[kMaxK];
+    uint32_t gbit[12];   // on a scalar cache line of its own in a BlockStaged
+    uint32_t pad[4];
+};
+// A staged pass's record: both, side by side (a table of offsets by itself cost
+// staged passes 0.5 %).  Unstaged passes, which can have very many narrow
+// blocks, read the short records: each is a scalar cache miss or a part of
+// one, and on one 2^11-amplitude tile 165 one- and two-qubit blocks took 88 us
+// with records of 128 bytes, 82 with short ones.
+struct BlockStaged {
+    BlockDev d;
+    BlockBits bits;
+};
+static_assert(sizeof(BlockStaged) == 128, "BlockStaged layout");
 
 // Launch arguments of one pass (passed by value).
 struct PassArgs {
@@ -182,6 +194,7 @@ struct qs_plan_s {
     // device copies (built on first use per dtype)
     int dev_ready[2] = {0, 0};
     qs::BlockDev *d_blocks[2] = {nullptr, nullptr};   // behind the operands, in d_pool's allocation
+    qs::BlockStaged *d_staged[2] = {nullptr, nullptr};   // the records of staged passes, behind those
     void *d_pool[2] = {nullptr, nullptr};
     size_t pool_bytes[2] = {0, 0};
     std::vector<qs::BlockDev> h_blocks[2];
@@ -203,7 +216,7 @@ void block_matrix(const std::vector<HGate> &gates, HBlock &b);
 // kernels_tile.hip: device copy of a plan's operands and block records
 qs_status plan_upload(qs_plan_s &p, qs_dtype dt);
 // what plan_upload copies: the operands (pool_bytes of them), then the block
-// records (h_blocks holds them too).  stage_lds: passes may stage their
+// records (h_blocks holds them too) in both forms.  stage_lds: passes may stage their
 // operands in LDS (the single-state pass kernel); the batch kernel reads them
 // from the pool.
 qs_status plan_image(qs_plan_s &p, qs_dtype dt, bool stage_lds, std::vector<unsigned char> &image);

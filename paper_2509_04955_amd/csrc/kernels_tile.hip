@@ -197,6 +197,9 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT, LEAN>())) void
         cst = reinterpret_cast<R *>(smem_raw + (size_t)tsize * sizeof(A) + kRedBytes);
     }
     const TileAligned tl{lds_addr(tile)};
+    auto record = [&](int b) -> const BlockDev * {
+        return CL ? &reinterpret_cast<const BlockStaged *>(blocks)[b].d : blocks + b;
+    };
     R sc = !ONE && pa.apply_scale ? (R)(*scale_in) : (R)1;
     const uint32_t my_li = threadIdx.x * APV;
     const bool active = NJ > 0 || my_li < tsize;   // small tiles: fewer vectors than threads
@@ -286,8 +289,9 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT, LEAN>())) void
         }
         __syncthreads();
         for (int b = 0; b < pa.nblocks; ++b) {
-            if (blocks[pa.block0 + b].kind == BK_SKIP) continue;   // folded into a group (uniform)
-            apply_block<R, WIDE, CL, NT, true, LEAN, ONE>(tl, T, blocks + pa.block0 + b, pool, base, cst, pa.cl_off);
+            const BlockDev *bd = record(pa.block0 + b);
+            if (bd->kind == BK_SKIP) continue;   // folded into a group (uniform)
+            apply_block<R, WIDE, CL, NT, true, LEAN, ONE>(tl, T, bd, pool, base, cst, pa.cl_off);
             __syncthreads();
         }
         // the store's addresses are formed anew from here on
@@ -379,8 +383,9 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT, LEAN>())) void
         }
         // ---- blocks ----
         for (int b = 0; b < pa.nblocks; ++b) {
-            if (blocks[pa.block0 + b].kind == BK_SKIP) continue;   // folded into a group (uniform)
-            apply_block<R, WIDE, CL, NT, true, LEAN>(tl, T, blocks + pa.block0 + b, pool, base, cst, pa.cl_off);
+            const BlockDev *bd = record(pa.block0 + b);
+            if (bd->kind == BK_SKIP) continue;   // folded into a group (uniform)
+            apply_block<R, WIDE, CL, NT, true, LEAN>(tl, T, bd, pool, base, cst, pa.cl_off);
             __syncthreads();
         }
         V ex[EX > 0 ? EX : 1];
@@ -1230,8 +1235,12 @@ bool pass_staged(const std::vector<HBlock> &blocks, const HPass &ps, qs_dtype dt
 namespace {
 qs_status build_image(qs_plan_s &p, qs_dtype dt, bool stage_lds, std::vector<unsigned char> &image);
 
-// where the block records lie in a plan's image, behind its operands
+// where the block records and those of staged passes lie in a plan's image,
+// behind its operands
 size_t blocks_offset(size_t pool_bytes) { return (pool_bytes + 255) / 256 * 256; }
+size_t staged_offset(size_t pool_bytes, size_t nblocks) {
+    return (blocks_offset(pool_bytes) + nblocks * sizeof(BlockDev) + 255) / 256 * 256;
+}
 
 // QS_TILE_LEAN=0: staged passes keep the general variants
 bool lean_enabled() {
@@ -1290,7 +1299,9 @@ qs_status plan_upload(qs_plan_s &p, qs_dtype dt) {
     // one allocation and one copy
     QS_HIP(hipMalloc(&p.d_pool[di], image.size()));
     QS_HIP(hipMemcpy(p.d_pool[di], image.data(), image.size(), hipMemcpyHostToDevice));
-    p.d_blocks[di] = reinterpret_cast<BlockDev *>((unsigned char *)p.d_pool[di] + blocks_offset(p.pool_bytes[di]));
+    unsigned char *base = (unsigned char *)p.d_pool[di];
+    p.d_blocks[di] = reinterpret_cast<BlockDev *>(base + blocks_offset(p.pool_bytes[di]));
+    p.d_staged[di] = reinterpret_cast<BlockStaged *>(base + staged_offset(p.pool_bytes[di], p.h_blocks[di].size()));
     p.dev_ready[di] = 1;
     return QS_OK;
 }
@@ -1299,6 +1310,7 @@ namespace {
 qs_status build_image(qs_plan_s &p, qs_dtype dt, bool stage_lds, std::vector<unsigned char> &image) {
     const int di = dt == QS_C64 ? 0 : 1;
     std::vector<BlockDev> hb(p.blocks.size());
+    std::vector<BlockStaged> staged(p.blocks.size());
     std::vector<float> pool32;
     std::vector<double> pool64;
     p.pass_wide[di].assign(p.passes.size(), 0);
@@ -1340,9 +1352,9 @@ qs_status build_image(qs_plan_s &p, qs_dtype dt, bool stage_lds, std::vector<uns
             for (int j = 0; j < d.k; ++j)
                 d.pos[j] = (int)(std::find(ps.tile.begin(), ps.tile.end(), blk.qubits[j]) - ps.tile.begin());
             const uint32_t amp = dt == QS_C64 ? 8 : 16;
-            for (int j = 0; j < d.k; ++j) d.pbit[j] = sw(1u << d.pos[j]) * amp;
+            for (int j = 0; j < d.k; ++j) staged[b].bits.pbit[j] = sw(1u << d.pos[j]) * amp;
             for (int q = 0, i = 0; q < ps.t && i < 12; ++q)
-                if (std::find(d.pos, d.pos + d.k, q) == d.pos + d.k) d.gbit[i++] = sw(1u << q) * amp;
+                if (std::find(d.pos, d.pos + d.k, q) == d.pos + d.k) staged[b].bits.gbit[i++] = sw(1u << q) * amp;
             if (dt == QS_C64) push_block<float>(blk, d, ps.t, dt, lds, pool32, wide);
             else push_block<double>(blk, d, ps.t, dt, lds, pool64, wide);
         }
@@ -1356,10 +1368,13 @@ qs_status build_image(qs_plan_s &p, qs_dtype dt, bool stage_lds, std::vector<uns
     }
     p.h_blocks[di] = hb;
     const size_t pbytes = dt == QS_C64 ? pool32.size() * sizeof(float) : pool64.size() * sizeof(double);
-    image.resize(blocks_offset(pbytes) + std::max<size_t>(1, hb.size()) * sizeof(BlockDev));
+    image.resize(staged_offset(pbytes, hb.size()) + std::max<size_t>(1, hb.size()) * sizeof(BlockStaged));
     if (pbytes)
         std::memcpy(image.data(), dt == QS_C64 ? (const void *)pool32.data() : (const void *)pool64.data(), pbytes);
     if (!hb.empty()) std::memcpy(image.data() + blocks_offset(pbytes), hb.data(), hb.size() * sizeof(BlockDev));
+    for (size_t b = 0; b < hb.size(); ++b) staged[b].d = hb[b];
+    if (!hb.empty())
+        std::memcpy(image.data() + staged_offset(pbytes, hb.size()), staged.data(), hb.size() * sizeof(BlockStaged));
     p.pool_bytes[di] = pbytes;
     return QS_OK;
 }
@@ -1454,13 +1469,15 @@ qs_status run_pass(qs_state_s &s, const qs_plan_s &p, const HPass &ps, const Pas
         prof_begin(s.stream, QS_PROF_TILE, 2 * S, flops);
     }
     unsigned long long *tickets = reinterpret_cast<unsigned long long *>(s.d_slots + kSlotTickets);
+    // staged variants read the records with LDS offsets
+    const BlockDev *records = pa.cl_len ? &p.d_staged[di]->d : p.d_blocks[di];
     if (L.k32)
         hipLaunchKernelGGL(L.k32, dim3(L.grid), dim3(L.threads), L.lds, s.stream, (float2 *)s.amp, L.ntiles, pa,
-                           p.d_blocks[di], (const float *)p.d_pool[di], scale, parts_out, tickets,
+                           records, (const float *)p.d_pool[di], scale, parts_out, tickets,
                            (unsigned long long)s.tickets);
     else
         hipLaunchKernelGGL(L.k64, dim3(L.grid), dim3(L.threads), L.lds, s.stream, (double2 *)s.amp, L.ntiles, pa,
-                           p.d_blocks[di], (const double *)p.d_pool[di], scale, parts_out, tickets,
+                           records, (const double *)p.d_pool[di], scale, parts_out, tickets,
                            (unsigned long long)s.tickets);
     prof_end(s.stream);
     QS_HIP(hipGetLastError());

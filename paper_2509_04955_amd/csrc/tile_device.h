@@ -732,7 +732,7 @@ __host__ __device__ constexpr int lds_row_part(int i) {
     return sizeof(R) == 4 ? i % 2 : (i / 4) % 2;
 }
 template <int K, typename R, int NT = TT, typename TL>
-__device__ __forceinline__ void mfma_block_lds(TL tl, int T, const BlockDev *bd, const R *As) {
+__device__ __forceinline__ void mfma_block_lds(TL tl, int T, const BlockBits *bits, const R *As) {
     using A = typename AmpOf<R>::A;
     using V4 = typename Mfma<R>::V4;
     constexpr int D = 1 << K;
@@ -744,7 +744,7 @@ __device__ __forceinline__ void mfma_block_lds(TL tl, int T, const BlockDev *bd,
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int gq = lane >> 4, jc = lane & 15;
-    const uint32_t *pb = bd->pbit, *gb = bd->gbit;
+    const uint32_t *pb = bits->pbit, *gb = bits->gbit;
     // input row 4 m + gq
     const uint32_t in_l = pick_lane<2>((uint32_t)gq, pb);
     uint32_t offB[NB];
@@ -827,7 +827,7 @@ __device__ __forceinline__ void mfma_block_lds(TL tl, int T, const BlockDev *bd,
 // each wave owns whole chunks: no barrier inside the block.  K = 4 keeps all
 // of A in registers for the block; K = 5 re-reads it per chunk.
 template <int K, typename R, int NT = TT, typename TL>
-__device__ __forceinline__ void mfma3m_block_lds(TL tl, int T, const BlockDev *bd, const R *As) {
+__device__ __forceinline__ void mfma3m_block_lds(TL tl, int T, const BlockBits *bits, const R *As) {
     using A = typename AmpOf<R>::A;
     using V4 = typename Mfma<R>::V4;
     static_assert(K == 4 || K == 5, "three-product GEMM needs 2^K >= 16");
@@ -840,7 +840,7 @@ __device__ __forceinline__ void mfma3m_block_lds(TL tl, int T, const BlockDev *b
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int gq = lane >> 4, jc = lane & 15;
-    const uint32_t *pb = bd->pbit, *gb = bd->gbit;
+    const uint32_t *pb = bits->pbit, *gb = bits->gbit;
     const uint32_t in_l = pick_lane<2>((uint32_t)gq, pb);   // input row 4 s + gq
     uint32_t offB[S];
 #pragma unroll
@@ -941,13 +941,13 @@ __device__ __forceinline__ void mfma3m_block_lds(TL tl, int T, const BlockDev *b
 constexpr int kBdPackFloats = 256 + 8 + 8;
 
 template <int K, int NT = TT, typename TL>
-__device__ __forceinline__ void bdiag_mfma_block(TL tl, int T, const BlockDev *bd, const float *Es) {
+__device__ __forceinline__ void bdiag_mfma_block(TL tl, int T, const BlockBits *bits, const float *Es) {
     constexpr int NPK = (1 << K) / 8;
     constexpr int CPI = staged_chunks<float>(K);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, jc = lane & 15;
-    const uint32_t *gb = bd->gbit;
+    const uint32_t *gb = bits->gbit;
     // per pack: this lane's A values, its 4 column offsets (with the part's
     // 4-byte shift), its 2 row offsets
     floatx4 a[NPK];
@@ -1094,13 +1094,15 @@ template <typename R, bool WIDE, bool CL = false, int NT = TT, bool PG = true, b
 __device__ __forceinline__ void apply_block(TL tile, int T, const BlockDev *bd,
                                             const R *__restrict__ pool, uint64_t gbase, const R *cst = nullptr,
                                             int cl_off = 0) {
+    // CL: the record is one of a BlockStaged
+    const BlockBits *bits = CL ? &reinterpret_cast<const BlockStaged *>(bd)->bits : nullptr;
     const int k = bd->k;
     const int kind = bd->kind;
     const R *U = pool + bd->mat_off;
     constexpr bool F32 = sizeof(R) == 4;
     if constexpr (LEAN && !F32) {
         if (kind == BK_MFMA) {
-            mfma_block_lds<3, R, NT>(tile, T, bd, cst + (bd->mat_off - cl_off));
+            mfma_block_lds<3, R, NT>(tile, T, bits, cst + (bd->mat_off - cl_off));
         } else if (kind == BK_BDIAG) {
             if (bd->sub == 1) bdiag_block<3, 1, R, NT>(tile, T, bd, U);
             else bdiag_block<3, 2, R, NT>(tile, T, bd, U);
@@ -1130,7 +1132,7 @@ __device__ __forceinline__ void apply_block(TL tile, int T, const BlockDev *bd,
     if constexpr (CL && F32) {
         if (kind == BK_BDMFMA) {
             const float *Es = cst + (bd->mat_off - cl_off);
-            if (bd->sub == 3) bdiag_mfma_block<4, NT>(tile, T, bd, Es);
+            if (bd->sub == 3) bdiag_mfma_block<4, NT>(tile, T, bits, Es);
             else if (bd->sub == 2) class_mfma_block<2, NT>(tile, T, bd, U, Es);
             else class_mfma_block<1, NT>(tile, T, bd, U, Es);
             return;
@@ -1139,10 +1141,10 @@ __device__ __forceinline__ void apply_block(TL tile, int T, const BlockDev *bd,
     if (kind == BK_MFMA) {
         if constexpr (CL) {
             const R *As = cst + (bd->mat_off - cl_off);
-            if (k == 3) mfma_block_lds<3, R, NT>(tile, T, bd, As);
-            else if (LEAN || k == 4) mfma3m_block_lds<4, R, NT>(tile, T, bd, As);
-            else if constexpr (NT > TT) mfma_block_lds<5, R, NT>(tile, T, bd, As);
-            else mfma3m_block_lds<5, R, NT>(tile, T, bd, As);
+            if (k == 3) mfma_block_lds<3, R, NT>(tile, T, bits, As);
+            else if (LEAN || k == 4) mfma3m_block_lds<4, R, NT>(tile, T, bits, As);
+            else if constexpr (NT > TT) mfma_block_lds<5, R, NT>(tile, T, bits, As);
+            else mfma3m_block_lds<5, R, NT>(tile, T, bits, As);
             return;
         } else if constexpr (F32 && !WIDE) {
             if (k == 4) mfma_block<4, R, NT>(tile, T, bd, U);
