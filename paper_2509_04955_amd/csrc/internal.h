@@ -89,11 +89,10 @@ struct BlockBits {
     uint32_t gbit[12];   // on a scalar cache line of its own in a BlockStaged
     uint32_t pad[4];
 };
-// A staged pass's record: both, side by side (a table of offsets by itself cost
-// staged passes 0.5 %).  Unstaged passes, which can have very many narrow
-// blocks, read the short records: each is a scalar cache miss or a part of
-// one, and on one 2^11-amplitude tile 165 one- and two-qubit blocks took 88 us
-// with records of 128 bytes, 82 with short ones.
+// A staged pass's record: both, side by side.  Unstaged passes, which can have
+// very many narrow blocks, read the short records: each is a scalar cache miss
+// or a part of one, and on one 2^11-amplitude tile 165 one- and two-qubit
+// blocks take 85 us with records of 128 bytes, 78 with short ones.
 struct BlockStaged {
     BlockDev d;
     BlockBits bits;

@@ -352,11 +352,13 @@ __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT, LEAN>())) void
             V ex[EX];
 #pragma unroll
             for (int i = 0; i < EX; ++i) ex[i] = ld_nt(gaddr(base, PF + i));
+            if constexpr (CL) touch_records(reinterpret_cast<const BlockStaged *>(blocks) + pa.block0, pa.nblocks);
 #pragma unroll
             for (int j = 0; j < PF; ++j) lds_put(j, pre[j]);
 #pragma unroll
             for (int i = 0; i < EX; ++i) lds_put(PF + i, ex[i]);
         } else {
+            if constexpr (CL) touch_records(reinterpret_cast<const BlockStaged *>(blocks) + pa.block0, pa.nblocks);
 #pragma unroll
             for (int j = 0; j < PF; ++j)
                 if ((uint32_t)j < nj) lds_put(j, pre[j]);
