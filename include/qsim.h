@@ -93,8 +93,9 @@ enum {
 
 typedef struct {
     int32_t k_max;        /* largest fused block, 1..6 (complex128: 1..5); 0 = 5 */
-    int32_t tile_qubits;  /* t: qubits held per tile in LDS; 0 = auto (10..13, c128 10..12, by n, dtype and k_max) */
-    int32_t low_qubits;   /* c: qubits 0..c-1 always in the tile (contiguous run); 0 = auto (2..6) */
+    int32_t tile_qubits;  /* t: qubits held per tile in LDS; 0 = auto (10..13, c128 10..12, by n, dtype, k_max
+                             and strategy; 13, c128 12, where low_qubits is given) */
+    int32_t low_qubits;   /* c: qubits 0..c-1 always in the tile (contiguous run); 0 = auto (2..6, by the same) */
     int32_t strategy;     /* QS_STRATEGY_* */
     int32_t renorm;       /* 1: FP64 norm of every pass, next pass rescales by 1/sqrt(norm) */
     int32_t dtype;        /* qs_dtype the plan is costed for (learned strategy); default c64 */

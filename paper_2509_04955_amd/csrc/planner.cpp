@@ -30,39 +30,66 @@ namespace qs {
 
 namespace {
 
-// Tile qubits and fixed low qubits where the caller leaves them open, for n
+// Tile qubits and fixed low qubits where the caller leaves both open, for n
 // qubits and blocks of up to k.  Geometric means over ansatz, random, UCC and
 // Fourier circuits, us per plan, against tiles of 2^13 (complex64) or 2^12
 // amplitudes with 6 low qubits:
-//   * 12..18 qubits: a pass is a few small workgroups in flight, and smaller
-//     tiles spread it over more CUs; states of this size stay in the caches, so
-//     short runs cost nothing (14 qubits complex64: 66 against 149 us for an
-//     ansatz of four layers; 16 qubits complex128: 126 against 239);
-//   * 19..22: the smallest tiles that still give every CU one or two
-//     (20 qubits complex64: 200 against 260; complex128 as noted below);
+//   * up to 16 qubits (complex128: 18): a pass is a few small workgroups in
+//     flight, and smaller tiles spread it over more CUs; states of this size
+//     stay in the caches, so short runs cost nothing (14 qubits complex64: 66
+//     against 149 us for an ansatz of four layers; 16 qubits complex128: 126
+//     against 239).  Exceptions are complex64 blocks of 4 and 6 qubits at 12
+//     qubits (random gates, k 4: 35 us in one tile against 45; an ansatz of
+//     six layers, k 6: 97 against 147) and of 4 at 13 (43 us in 2^11 tiles
+//     against 61), where the matrix cores do more in larger tiles;
+//   * to 22: the smallest tiles that still give every CU one or two (20 qubits
+//     complex64: 200 against 260; complex128 as noted below);
 //   * above: as many qubits as the LDS allows, fewest passes, and runs of a
 //     cache line (24 qubits complex64: 1700 against 2000).  Complex128 blocks
 //     of four and five qubits are held back by waves, not by passes: smaller
 //     tiles (24 qubits, k 5: 4.1 against 6.3 ms, 26 qubits: 18.7 against 25.6;
-//     k 3 is fastest at 2^12: 6.2 against 7.1 ms).
+//     k 3 is fastest at 2^12: 6.2 against 7.1 ms).  Single circuits can go the
+//     other way by a pass more: random gates at 24 qubits, k 4, 1.34 against
+//     1.17 ms, the Fourier transform at 26, k 5, 26.0 against 24.3.
 // One tile holds states of up to 11 qubits (11 qubits: 44 us against 55 us in
 // two tiles).
-void auto_shape(int n, qs_dtype dt, int k, int &t, int &low) {
-    if (n <= 11) {
-        t = 11;
+// A plan of single gates (k: its widest) has the least work per pass: 2^11
+// tiles from 24 qubits complex128 (26 qubits: 17.3 against 18.2 ms at 2^12).
+// rot: a plan of rotations with an X part.  They need few qubits in the tile
+// and do little with them there, so passes decide.  One tile up to 13 qubits
+// (complex128: 12; 40 exponentials on 12 qubits 42 us, in 2^10 tiles 67), and
+// complex128 states from 23 qubits in 2^12 tiles with 3 low qubits (24 qubits:
+// 1.66 ms, in 2^11 tiles with 5 2.19).
+void auto_shape(int n, qs_dtype dt, int k, bool single, bool rot, int &t, int &low) {
+    const bool c64 = dt == QS_C64;
+    if (n <= 11 || (rot && n <= (c64 ? 13 : 12))) {
+        t = std::max(n, 11);
         low = 6;
-    } else if (n <= (dt == QS_C64 ? 16 : 18)) {
+    } else if (c64 && !rot && ((n == 12 && (k == 4 || k == 6)) || (n == 13 && k == 4))) {
+        t = n == 12 ? 12 : 11;
+        low = 3;
+    } else if (n <= (c64 ? 16 : 18)) {
         t = 10;
         low = 2;
-    } else if (dt == QS_C64) {
+    } else if (c64) {
         t = n <= 20 ? 11 : 13;
         low = n <= 20 ? 3 : 4;
     } else {
         // 20 qubits, k 5: 352 us at 2^12 against 390; k 2..4: 262..334 against 235..295 at 2^11
-        t = n == 19 || (n == 20 && k < 5) || (n >= 23 && k >= 4) ? 11 : 12;
-        low = n >= 23 && k >= 5 ? 5 : 3;
+        const bool wide = k >= 4 && !rot;
+        t = n == 19 || (n == 20 && k < 5) || (n >= 23 && wide) || (n >= 24 && single) ? 11 : 12;
+        low = n >= 23 && wide && k >= 5 ? 5 : 3;
     }
 }
+
+// The same where only one of the two is open.  A given tile takes the low
+// qubits of the rule above (five families of circuits, 10..26 qubits, tiles of
+// 2^10..2^14, k 3 and 5: on average 0 to 30 % faster than six low qubits at
+// every size, 12 of 576 plans slower, by 2 to 9 %).  Given low qubits keep the
+// largest usual tile: the sizes above were chosen with their low qubits, and
+// with others as many plans lost as won (12 qubits complex64, 4 low qubits, k
+// 3: 53 against 67 us; 24 qubits complex128, 2 low, k 5: 4.0 against 5.5 ms).
+constexpr int usual_tile(qs_dtype dt) { return dt == QS_C128 ? 12 : 13; }
 
 }  // namespace
 
@@ -436,9 +463,19 @@ qs_status build_plan(qs_plan_s &p) {
     const int kcap = dt == QS_C128 ? kMaxK128 : kMaxK;
     if (o.k_max == 0) o.k_max = 5;
     QS_CHECK(o.k_max >= 1 && o.k_max <= kcap, QS_EINVAL, "k_max %d outside 1..%d", o.k_max, kcap);
+    int gate_max = 1;
+    for (const HGate &g : p.gates) gate_max = std::max(gate_max, g.nq);
+    const bool single = o.strategy == QS_STRATEGY_NONE;
+    // a plan of rotations: most gates lie in rotations that keep an X part
+    // (where the tile is open it holds every X part of up to 8 qubits)
+    std::vector<PauliWindow> win;
+    const bool open = o.tile_qubits == 0 && o.strategy == QS_STRATEGY_PAULI;
+    if (open) win = pauli_windows(p.gates, o.k_max, std::min(8, p.n - 1));
+    size_t inside = 0;
+    for (const PauliWindow &w : win) inside += (size_t)(w.end - w.begin);
     int auto_t, auto_low;
-    auto_shape(p.n, dt, o.k_max, auto_t, auto_low);
-    if (o.tile_qubits == 0) o.tile_qubits = o.low_qubits > auto_t ? (dt == QS_C128 ? 12 : 13) : auto_t;
+    auto_shape(p.n, dt, single ? gate_max : o.k_max, single, 2 * inside > p.gates.size(), auto_t, auto_low);
+    if (o.tile_qubits == 0) o.tile_qubits = o.low_qubits ? usual_tile(dt) : auto_t;
     const int tcap = dt == QS_C128 ? kMaxTile128 : kMaxTile;
     QS_CHECK(o.tile_qubits >= 2 && o.tile_qubits <= tcap, QS_EINVAL, "tile_qubits %d outside 2..%d",
              o.tile_qubits, tcap);
@@ -452,12 +489,10 @@ qs_status build_plan(qs_plan_s &p) {
     QS_CHECK(o.strategy >= QS_STRATEGY_NONE && o.strategy <= QS_STRATEGY_PAULI, QS_EINVAL, "strategy %d unknown",
              o.strategy);
     QS_CHECK(o.commute == 0 || o.commute == 1, QS_EINVAL, "commute must be 0 or 1 (got %d)", o.commute);
-    int wmax = o.k_max;
-    for (const HGate &g : p.gates) wmax = std::max(wmax, g.nq);
-    std::vector<PauliWindow> win;
+    int wmax = std::max(o.k_max, gate_max);
     if (o.strategy == QS_STRATEGY_PAULI) {
         // X parts up to 8 qubits and below the tile (qubit 0 keeps a slot)
-        win = pauli_windows(p.gates, o.k_max, std::min(8, std::min(o.tile_qubits, p.n) - 1));
+        if (!open) win = pauli_windows(p.gates, o.k_max, std::min(8, std::min(o.tile_qubits, p.n) - 1));
         for (const PauliWindow &w : win) wmax = std::max(wmax, __builtin_popcountll(w.x));
     }
     if (t < p.n)
