@@ -44,7 +44,7 @@ enum : uint8_t { G_DENSE = 0, G_REAL = 1, G_RX = 2, G_NOT = 3, G_PHASE = 4, G_DI
 constexpr int kMaxSlots = 4;           // register qubits of a stage, at most
 constexpr int kMaxStages = 56;
 constexpr int kMinQubits = 4;          // smaller states: sweeps
-constexpr int kSweepQubits = 22;       // states beyond the caches: two light gates are cheaper as sweeps
+constexpr int kSweepQubits = 22;       // states beyond the L2s: two light gates are cheaper as sweeps (few_sweeps)
 constexpr int kRunLookahead = 128;     // gates left out of a run before its search ends
 constexpr uint64_t kMaxRunTiles = 1u << 20;   // tiles of one launch (a grid holds fewer than 2^32 threads)
 constexpr int kNoQubit = 63;           // outside-qubit field of a gate without one (no state has such a qubit)
@@ -432,6 +432,42 @@ void run_shape(int n, qs_dtype dt, int &t, int &ns) {
     t = std::min(t, n);
 }
 
+// What a gate's own sweep reads and writes, in states, with whole 128-byte
+// lines: a control, phase or SWAP qubit among the lowest leaves no line out.
+double sweep_lines(const RunItem &it, int n, qs_dtype dt) {
+    const uint64_t in_line = dt == QS_C64 ? 15 : 7;
+    switch (it.kind) {
+    case G_SWAP: return it.qubits & in_line ? 2.0 : 1.0;
+    case G_DIAG: return 2.0;
+    default: break;
+    }
+    if (!it.mask) return 2.0;   // an uncontrolled target
+    double w = 2.0;
+    for (uint64_t b = it.mask & ~in_line; b; b &= b - 1) w *= 0.5;
+    // complex64 sweeps of controlled gates lose a quarter on states that the
+    // memory-side cache holds (128 and 256 MiB)
+    return it.targets && dt == QS_C64 && (n == 24 || n == 25) ? 1.25 * w : w;
+}
+
+// Whether the gates of a would-be run go as sweeps of their own.  A run moves
+// 2 states; two sweeps that move one each take the same traffic with less work
+// around it, and the second finds part of the first's output in a cache.
+// Two SWAPs, far qubits: 26 qubits complex64 158 us as sweeps, 199 as a run,
+// 23 qubits 18 and 28, 22 qubits complex128 18 and 27; two controlled gates on
+// 25 qubits: complex128 156 and 206, complex64 96 and 70.
+bool few_sweeps(const std::vector<const RunItem *> &taken, int n, qs_dtype dt) {
+    if (n < kSweepQubits) return false;
+    double sweep = 0, lines = 0;
+    for (const RunItem *it : taken) {
+        sweep += it->sweep;
+        lines += sweep_lines(*it, n, dt);
+    }
+    // more than two sweeps only on states that no cache holds (four CZ on 24
+    // qubits complex64 47 us against 44, on 26 qubits 176 against 202)
+    const bool far = n > (dt == QS_C64 ? 25 : 24);
+    return sweep <= 1.5 || (lines <= 2.0 && (taken.size() == 2 || far) && (dt == QS_C128 || n > kSweepQubits));
+}
+
 int item_words(const RunItem &it, qs_dtype dt) {
     if (it.kind == G_SWAP) return 3 * gate_words<float>(G_NOT);
     return dt == QS_C64 ? gate_words<float>(it.kind) : gate_words<double>(it.kind);
@@ -574,7 +610,6 @@ qs_status launch_gates(qs_state_s &s, const std::vector<HGate> &gates) {
         // list scheduling, as for passes of blocks: a gate that does not fit
         // waits, and so does every later gate that shares a qubit with it
         uint64_t cur = low, blocked = 0;
-        double sweep = 0;
         int words = 0;
         taken.clear();
         next.clear();
@@ -602,7 +637,6 @@ qs_status launch_gates(qs_state_s &s, const std::vector<HGate> &gates) {
             }
             if (!it->alone && !(it->qubits & blocked) && __builtin_popcountll(cur | it->targets) <= t) {
                 cur |= it->targets;
-                sweep += it->sweep;
                 words += need;
                 taken.push_back(it);
             } else {
@@ -614,7 +648,7 @@ qs_status launch_gates(qs_state_s &s, const std::vector<HGate> &gates) {
         qs_status st = QS_OK;
         if (alone) {
             st = launch_plain(s, *alone->src);
-        } else if (taken.size() == 1 || (s.n >= kSweepQubits && sweep <= 1.5)) {
+        } else if (taken.size() == 1 || few_sweeps(taken, s.n, s.dtype)) {
             for (const RunItem *it : taken) {
                 st = launch_plain(s, *it->src);
                 if (st != QS_OK) return st;

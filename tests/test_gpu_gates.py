@@ -90,3 +90,17 @@ def test_captured_list_replays(Q):
             assert torch.equal(torch.view_as_real(st.tensor), torch.view_as_real(ref.tensor))
     st.close()
     ref.close()
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n", [22, 23])
+def test_two_light_gates(Q, oracle, n, dtype):
+    """Lists of two to four gates that move half of the state or less each: as
+    sweeps or as a run, on near and far qubits."""
+    for kinds in (("swap", "swap"), ("swap", "cx"), ("p", "cu"), ("cz",) * 4):
+        for b in (0, n - 8):
+            c = qsynth.Circuit(n)
+            for i, k in enumerate(kinds):
+                q = (b + 2 * i, b + 2 * i + 1)
+                c.add(k, q if k != "p" else q[:1], {"p": (0.4,), "cu": (0.1, 0.2, 0.3)}.get(k, ()))
+            _check(Q, oracle, c, dtype, seed=n)
