@@ -194,3 +194,26 @@ def test_batch_holds_its_operands_once(Q):
     b.close()
     one = states * gates * 128 * 128 * 4
     assert used <= 1.5 * one, (used, one)   # less where the driver reuses chunks freed before
+
+
+@pytest.mark.parametrize("dtype,tol", [(0, 1e-6), (1, 1e-12)])
+def test_batch_long_items(Q, oracle, dtype, tol):
+    """Items of several tiles and of several cosets: four 19-qubit states in
+    64-amplitude tiles are more than 48 tiles per CU in a level, and 400 terms
+    on each give more than 16 full cosets per CU; beside them a state of one
+    full coset (14 qubits complex64, 13 complex128) and one of two.
+    Tolerances as for the uneven batch above."""
+    cus, _, _ = Q.qs_device_query()
+    one = 14 if dtype == 0 else 13
+    ns = (one, one + 1, 19, 19, 19, 19)
+    assert 4 * 2 ** (19 - 6) >= 2 * 24 * cus and 4 * (400 // 9) * 2 ** (19 - one) >= 2 * 8 * cus
+    circuits = [qsynth.random_circuit(n, 25, seed=70 + i) for i, n in enumerate(ns)]
+    hams = [qsynth.random_pauli_sum(n, 400 if n == 19 else 30, seed=(7, i)) for i, n in enumerate(ns)]
+    b = Q.Batch(circuits, hams, Q.opts(k_max=3, tile_qubits=6, low_qubits=2, dtype=dtype))
+    E = b.run()
+    assert np.array_equal(E, b.run())
+    for i, (c, h) in enumerate(zip(circuits, hams)):
+        psi, e = _oracle_energy(oracle, c, h)
+        assert abs(E[i] - e) <= tol * max(1, abs(e)), (i, c.n, E[i], e)
+        assert oracle.max_abs(psi, b.amplitudes(i)) <= (1e-5 if dtype == 0 else 1e-12)
+    b.close()
