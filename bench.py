@@ -368,6 +368,24 @@ def gate_by_gate(Q, st, circ):
     return run
 
 
+def gate_by_gate_graph(Q, n, dtype, circ):
+    """The plain method from |0...0> on a state of its own, its sweeps recorded
+    once and replayed: on small states a sweep takes less than the host's call.
+    Returns the state and the call."""
+    import torch
+
+    stream, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        st = Q.State(n, dtype)
+        run = gate_by_gate(Q, st, circ)
+        run()   # the kernels' first use stays out of the recording
+        stream.synchronize()
+        with torch.cuda.graph(g, stream=stream):
+            st.set_basis(0)
+            run()
+    return st, g.replay
+
+
 def plain12_mode(a):
     """The plain method's configuration: 12-qubit random circuit (20 layers of
     H or RZ per qubit + 6 CNOTs), complex128 from |0...0>, as one gate list.
@@ -412,8 +430,8 @@ def families_mode(a):
     """The paper's circuit families at 20, 25 and 30 qubits, complex64: HEA
     (5 layers RX/RY/RZ + staggered CNOT), QAOA MaxCut (3-regular graph, p = 3)
     and QFT.  Gate-count compression of the contraction at k_max = 2 and at
-    the autotuned width; time gate by gate (one sweep per gate), with every
-    gate a block of its own streamed in the same tile passes (several gates
+    the autotuned width; time gate by gate (one sweep per gate, replayed as a
+    graph), with every gate a block of its own streamed in the same tile passes (several gates
     per sweep, no contraction: the role of the paper's multi-gate ablation),
     fused, fused with Pauli-rotation contraction (strategy 3), and fused with
     commutation-aware contraction (the commute option, autotuned); and the
@@ -447,9 +465,10 @@ def families_mode(a):
             com = Q.qs_contract(n, gl, Q.opts(k_max=best_c.k_max, tile_qubits=best_c.tile_qubits,
                                               low_qubits=best_c.low_qubits, commute=1))
             cinfo = Q.qs_plan_info_get(com)
+            st, plain = gate_by_gate_graph(Q, n, Q.QS_C64, c)
+            ms_plain = _timed(plain)
+            st.close()
             st = Q.State(n, Q.QS_C64)
-            plain = gate_by_gate(Q, st, c)
-            ms_plain = _timed(lambda: (st.set_basis(0), plain()))
             ms_list = _timed(lambda: (st.set_basis(0), st.apply_gates(gl)))
             ms_smgp = _timed(lambda: (st.set_basis(0), st.apply_gates_smgp(gl)))
             ms_multi = _timed(lambda: (st.set_basis(0), st.apply_plan(multi)))

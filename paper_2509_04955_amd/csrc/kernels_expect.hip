@@ -175,6 +175,8 @@ __device__ __forceinline__ double diag_sum(const V *L, uint32_t t, uint32_t size
 }
 
 // ---- one coset: registers, LDS, terms ----------------------------------------
+// The parts of k_expect_jobs.  k_expect_coset below has the same steps written
+// out: built from these functions it was 1.5 % slower on a 28-qubit sum.
 //   V   cf2 (complex64) or cd2 (complex128)
 //   T   threads per workgroup
 //   NA  amplitudes each thread stages per coset

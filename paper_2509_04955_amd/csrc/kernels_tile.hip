@@ -129,6 +129,16 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 // writes, and the added waves fill their gaps: brickwork on 28 qubits
 // complex64 1.17 -> 1.13 ms a pass, random circuits on 27 qubits complex128
 // 0.99 -> 0.94 ms.
+//
+// ONE: a launch that gives every tile its own resident workgroup (states of up
+// to about 2^21 amplitudes).  Nothing is left to hand out or to prefetch, so
+// tile and workgroup share a number: no tickets (two dependent atomics on one
+// address by every workgroup before its first load) and no second read of the
+// tile in place of a next one.  Such a pass may also take the sum of the
+// previous pass's norm partials upon itself (pa.nsum of them, behind its tile
+// loads) instead of a reduction launch between the two: scale_in is then the
+// partials.  59 passes on 22 qubits complex64 (2^13 tiles): 45 -> 24 us a pass
+// with its norm; 10 passes on 19 qubits complex128: 45 -> 35 us.
 template <typename R, bool WIDE, int NJ, bool CL, int NT = TT, bool LEAN = false>
 constexpr int tile_waves() {
     if (LEAN) return 4;
@@ -145,16 +155,6 @@ constexpr int tile_waves() {
 // kTileAlign (block code then forms addresses with OR and XOR alone).
 constexpr size_t kRedBytes = 128 + 16;   // NT / 64 doubles for up to 1024 threads, two ticket slots
 
-//
-// ONE: a launch that gives every tile its own resident workgroup (states of up
-// to about 2^21 amplitudes).  Nothing is left to hand out or to prefetch, so
-// tile and workgroup share a number: no tickets (two dependent atomics on one
-// address by every workgroup before its first load) and no second read of the
-// tile in place of a next one.  Such a pass may also take the sum of the
-// previous pass's norm partials upon itself (pa.nsum of them, behind its tile
-// loads) instead of a reduction launch between the two: scale_in is then the
-// partials.  59 passes on 22 qubits complex64 (2^13 tiles): 45 -> 26 us a pass
-// with its norm; 10 passes on 19 qubits complex128: 45 -> 35 us.
 template <typename R, bool WIDE, int NJ, bool CL, int NT = TT, bool ONE = false, bool LEAN = false>
 __global__ __launch_bounds__(NT, (tile_waves<R, WIDE, NJ, CL, NT, LEAN>())) void k_tile_pass(
     typename AmpOf<R>::A *__restrict__ psi, uint64_t ntiles, PassArgs pa, const BlockDev *__restrict__ blocks,
@@ -508,8 +508,8 @@ using TileKernel = void (*)(typename AmpOf<R>::A *, uint64_t, PassArgs, const Bl
                             double *, unsigned long long *, unsigned long long);
 
 // Kernel variant for a pass: register footprint (wide), LDS-staged operands
-// (cl), a workgroup per tile (ONE) and, for the narrow variant and wide ONE
-// passes of complex128, the compile-time vector count.
+// (cl), a workgroup per tile (ONE) and, for the narrow variant, the
+// compile-time vector count.
 template <typename R, bool ONE>
 TileKernel<R> pick_tile_kernel(bool wide, int t, bool cl, bool lean, int &threads, bool &static_tile) {
     constexpr int APV = sizeof(R) == 4 ? 2 : 1;

@@ -105,7 +105,7 @@ __host__ __device__ __forceinline__ uint32_t sw(uint32_t li) { return li ^ (((li
 // tile at an LDS address aligned to kTileAlign, above every tile size, so
 // base + (g ^ o) = (base | g) ^ o: a group costs one OR and an access one XOR
 // (an LDS base that is only known at link time, as a dynamic region's, would
-// otherwise cost an add per access).  TilePtr places a tile at any address.
+// otherwise cost an add per access).
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
 constexpr uint32_t kTileAlign = 1u << 17;
 
@@ -117,15 +117,6 @@ struct TileAligned {
     template <typename T>
     __device__ __forceinline__ T *at(uint32_t h, uint32_t o) const {
         return (T *)(lds_u8 *)(uintptr_t)(h ^ o);
-    }
-};
-
-struct TilePtr {
-    unsigned char *base;
-    __device__ __forceinline__ uint32_t grp(uint32_t g) const { return g; }
-    template <typename T>
-    __device__ __forceinline__ T *at(uint32_t h, uint32_t o) const {
-        return reinterpret_cast<T *>(base + (h ^ o));
     }
 };
 

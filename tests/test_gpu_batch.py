@@ -1,4 +1,4 @@
-"""GPU parity of the batched persistent path (one hipGraph launch): every
+"""GPU parity of the batched path (one hipGraph launch): every
 state's energy and amplitudes against the FP64 oracle, for uneven qubit
 counts, repeated launches (determinism) and the autotuned plan choice."""
 import numpy as np
