@@ -202,7 +202,10 @@ qs_status qs_apply_plan(qs_state s, qs_plan p);
 /* Energy sum_k coeff[k] <psi|P_k|psi> / <psi|psi> of a Pauli sum; P_k has X or
  * Y on the set bits of x[k], Z or Y on the set bits of z[k] (Y where both).
  * FP64 accumulation; out_terms (optional, n_terms entries) receives each
- * <P_k>.  Synchronous. */
+ * <P_k>.  Synchronous.  The state itself is only read: threads may call this
+ * for one state at once (they take turns), as long as none changes it.  A
+ * state keeps the device tables of its sums (at most about 10 MB) and, from
+ * the second sum on, pinned memory for the results; both go with it. */
 qs_status qs_expect_pauli_sum(qs_state s, const uint64_t *x, const uint64_t *z,
                               const double *coeff, size_t n_terms, double *out,
                               double *out_terms);
