@@ -93,7 +93,7 @@ def test_captured_list_replays(Q):
 
 
 @pytest.mark.parametrize("dtype", [0, 1])
-@pytest.mark.parametrize("n", [22, 23])
+@pytest.mark.parametrize("n", [21, 22, 23])
 def test_two_light_gates(Q, oracle, n, dtype):
     """Lists of two to four gates that move half of the state or less each: as
     sweeps or as a run, on near and far qubits."""
